@@ -112,6 +112,7 @@ struct KArgs {
   int comm_tm_last;           // owner-write (column splits): tokens of the last split's
   int tasks_last;             //   tasks (finer, so that the launch ends evenly) and their count
   u64* epoch_word;            // the workspace's last completed launch epoch
+  u64* map_epoch;             // small batches: the epoch the first launch built the inverse map with
   uint32_t* done_ctr;         // workgroups of this launch that have finished
   uint32_t* start_ctr;        // workgroups of this launch that have started
   int delay_mod;              // debug: compute workgroups c % delay_mod == 0 delay
@@ -1894,6 +1895,8 @@ __global__ void pack_w1_kernel(const uint16_t* src, uint16_t* dst, long long n, 
   }
 }
 
+#include "small_batch.h"
+
 // Zeroes n words at p, except the 64-bit word at word index epoch_at (when
 // epoch_at + 1 < n), which takes `epoch`.
 __global__ void fill_zero_kernel(uint32_t* p, size_t n, size_t epoch_at, u64 epoch) {
@@ -1968,7 +1971,7 @@ bool make_layout(const moe_workload_t* wl, Layout* L) {
   L->status = off;   // word 0: status bits; bytes 4..255: reserved;
                      // 256..319: per-split consumer task counters;
                      // 320: launch epoch (u64); 328: finished workgroups;
-                     // 332: started workgroups
+                     // 332: started workgroups; 336: small batches' map epoch (u64)
   off += 512;
   L->wg_flags = off;
   off += (size_t)kMaxGrid * 4;
@@ -2286,6 +2289,62 @@ int validate_args(const void* x_perm, const void* w2, const int32_t* expert_offs
   return MOE_OK;
 }
 
+// ---- launches of small and medium batches (small_batch.h) -----------------------
+template <class C, class Args>
+long long small_units(const Args& a) {
+  // the most tiles that `rows` rows in at most min(E, rows) experts make
+  const long long n = a.E < a.rows ? a.E : a.rows;
+  return ((a.rows - n) / C::BM + n) * ((a.nsplit + C::BN - 1) / C::BN);
+}
+template <class C, class Args>
+hipError_t launch_small_tile(const Args& a, hipStream_t s) {
+  long long grid = (small_units<C>(a) + 7) / 8 * 8;   // eight equal XCD shares
+  if (grid < 8) grid = 8;
+  hipLaunchKernelGGL((small_gemm_kernel<C, Args>), dim3((unsigned)grid), dim3(C::kThr), 0, s, a);
+  return hipGetLastError();
+}
+using SmallTile128 = SmallTile<128, 128, 8, 4, 2>;   // 64 KB of LDS, two per CU
+using SmallTile64 = SmallTile<64, 128, 8, 4, 2>;     // 48 KB, three per CU
+using SmallTile64Deep = SmallTile<64, 128, 8, 4, 3>; // 72 KB, two per CU
+using SmallTileNarrow = SmallTile<64, 64, 4, 2, 4>;  // 64 KB, two per CU
+
+// The tile: 128 rows where the experts hold more than 64 rows on average and
+// such tiles still give every CU one; else 64 rows, with the deeper ring
+// while there are too few for three per CU; and 64 x 64 where not even those
+// fill the CUs.  Measured (us): H = 2048, I = 704, E = 32, top-6, T = 512 (96
+// rows per expert) 26.5 with 128 rows, 29.0 with 64; T = 256 (48) 23.4 / 22.3;
+// H = 1024, I = 512, E = 32, top-8, T = 64 (312 tiles) 13.4 with the shallow
+// ring, 12.4 with the deep one, and T = 256, 2048 columns (624 and more)
+// 22.3 / 23.4; the up-projection of H = 1352, I = 336, E = 11, T = 256 (132
+// 64 x 128 tiles) 11.5 with them, 9.8 with 64 x 64.
+template <class Args>
+hipError_t launch_small_gemm(const Args& a, int cus, hipStream_t s) {
+  const long long n = a.E < a.rows ? a.E : a.rows;
+  if (a.rows > 64 * n && small_units<SmallTile128>(a) >= cus)
+    return launch_small_tile<SmallTile128>(a, s);
+  const long long units = small_units<SmallTile64>(a);
+  if (units < cus) return launch_small_tile<SmallTileNarrow>(a, s);
+  return units < 2 * cus ? launch_small_tile<SmallTile64Deep>(a, s)
+                         : launch_small_tile<SmallTile64>(a, s);
+}
+
+// 256 x 256 tiles of an average routing (half a tile's rows of padding per
+// expert), over N columns.
+long long expected_tiles(long long rows, int E, int N) {
+  const long long n = E < rows ? E : rows;
+  return (2 * rows + kBM * n) * ((N + kBN - 1) / kBN) / (2 * kBM);
+}
+
+// The stage runs as small tiles up to about four 256 x 256 tiles per CU:
+// beyond that the larger tile's lower operand traffic and the combine under
+// the last tiles win.  Measured (us, persistent / small tiles): 3.5 tiles per
+// CU (H = 2048, I = 704, E = 32, T = 4096) 123 / 118, 4.1 (H = 1024, I = 256,
+// T = 8192) 104 / 93, 4.25 (H = 1024, I = 512, E = 32, T = 8192) 132 / 141,
+// 4.5 (H = 2048, I = 704, E = 30, top-4, T = 8192) 155 / 178.
+bool small_stage(long long rows, int E, int H, int cus) {
+  return expected_tiles(rows, E, H) <= 4LL * cus;
+}
+
 // `layout_slot`: where the workspace's last layout is kept when the
 // workspace is the library's own scratch (NULL: the per-address record).
 int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
@@ -2358,9 +2417,13 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
   a.rows = L.rows;
   a.max_tiles = L.max_tiles;
   a.spin_limit = 4000000;
+  bool wait_env = false;   // a debugging aid of the persistent kernel's waits is set
   if (const char* s = std::getenv("MOE_GEMM2_SPIN_LIMIT")) {
     long long v = std::atoll(s);
-    if (v > 0) a.spin_limit = v;
+    if (v > 0) {
+      a.spin_limit = v;
+      wait_env = true;
+    }
   }
   a.T = wl->T;
   a.H = wl->H;
@@ -2394,6 +2457,7 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
     a.tasks_per_split = bt.tasks;
   }
   a.epoch_word = reinterpret_cast<u64*>(ws + L.status + 320);
+  a.map_epoch = reinterpret_cast<u64*>(ws + L.status + 336);
   a.done_ctr = reinterpret_cast<uint32_t*>(ws + L.status + 328);
   a.start_ctr = reinterpret_cast<uint32_t*>(ws + L.status + 332);
   a.delay_mod = 1;
@@ -2405,6 +2469,7 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
     if (std::sscanf(s, "%lld:%lld", &m, &t) == 2 && m >= 1 && t > 0) {
       a.delay_mod = (int)(m < 4096 ? m : 4096);
       a.delay_ticks = t < 1000000 ? t : 1000000;
+      wait_env = true;
     }
   }
 
@@ -2419,6 +2484,32 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
     clear = workspace_needs_clear(workspace, sig);
   }
   if (clear && zero_async(workspace, L.Y, s) != hipSuccess) return MOE_ERR_HIP;
+  // Small and medium batches with no dedicated consumers asked for run as two
+  // launches without waits (the debugging aids act on the persistent
+  // kernel's waits, so they keep it).
+  if (!trace && num_consumers <= 0 && mode != 1 && !wait_env &&
+      small_stage(L.rows, wl->E, wl->H, d.cus)) {
+    a.nsplit = wl->H;
+    a.ysplit = round_up_line(wl->H);   // one segment; fits the column-split layout
+    a.ypitch = a.ysplit + kYPad;
+    hipError_t e = launch_small_gemm(a, d.cus, s);
+    if (e == hipSuccess) {
+      const long long units = (long long)wl->T * ((wl->H + 255) / 256);
+      hipLaunchKernelGGL(small_combine_kernel,
+                         dim3((unsigned)((units + kSmallCombineWaves - 1) / kSmallCombineWaves)),
+                         dim3(kSmallCombineWaves * 64), 0, s, a);
+      e = hipGetLastError();
+    }
+    if (e == hipSuccess) return C;
+    // the first launch may have run without the second: the workspace's
+    // counters are then those of an unfinished epoch, so clear them next time
+    std::lock_guard<std::mutex> lk(g_ws_mu);
+    if (layout_slot)
+      *layout_slot = 0;
+    else
+      g_ws_layout.erase((uintptr_t)workspace);
+    return MOE_ERR_HIP;
+  }
   hipLaunchKernelGGL(moe_gemm2_fused, dim3(C + P), dim3(kThreads), 0, s, a);
   if (hipGetLastError() != hipSuccess) return MOE_ERR_HIP;
   return C;

@@ -1,0 +1,459 @@
+// The stage and the up-projection for small and medium batches (included by
+// moe_gemm2.hip, inside its anonymous namespace, after its helpers).
+//
+// What bounds such a launch: below about 64 rows per expert the weights (W2
+// of 32 experts at H = 2048, I = 704 is 92 MB, 18.6 us at the rate a large
+// copy reaches here), above it the tiles' operand loads.  The persistent
+// kernel's 256 x 256 tiles give a workgroup 16-20 us of work whatever the
+// rows in them, and its publish, readiness and acquire another 10-15 us.
+// Here one launch runs the grouped GEMM with small tiles, one workgroup per
+// tile and two or three workgroups per CU, so that one's loads cover
+// another's start, epilogue and waits; a second launch combines, one wave
+// per token and 256 columns.  The kernel boundary is the only dependency:
+// no flags, no waits, nothing resident.  (The two launches run back to back
+// on the GPU: no gap in a kernel trace.)
+//
+// Every output element is the same chain as in the persistent kernel: the
+// same 32x32x16 MFMAs over the whole reduction in the same order, Y rounded
+// once to bf16, the rows of a token summed in ascending order.  So a
+// reduction is never split over waves, and the results are bitwise equal.
+//
+// Measured (us, GPU time, persistent kernel -> this path), H = 2048, I = 704,
+// E = 32, top-6, uniform routing: T = 1 36.7 -> 9.8, 8 40.7 -> 17.9,
+// 64 44.0 -> 21.3, 256 46.4 -> 22.3, 512 49.6 -> 26.5, 1024 55.9 -> 45,
+// 2048 80 -> 71, 4096 123 -> 118; its up-projection T = 1 44.3 -> 12.3,
+// 64 46.6 -> 28.4, 256 47.3 -> 29.7, 512 48.2 -> 33.5.
+#pragma once
+
+// A tile of BM rows x BN columns, its NW waves WNW along the columns, a ring
+// of S 64-deep stages in LDS (S - 1 of them in flight).
+
+template <int BM_, int BN_, int NW_, int WNW_, int S_>
+struct SmallTile {
+  static constexpr int BM = BM_, BN = BN_, NW = NW_, WNW = WNW_, S = S_;
+  static constexpr int WMW = NW / WNW;
+  static constexpr int WN = BN / WNW, WM = BM / WMW;   // a wave's columns and rows
+  static constexpr int NB = WN / 32, MB = WM / 32;
+  static constexpr int kThr = NW * 64;
+  static constexpr int XL = BM / 8 / NW, WL = BN / 8 / NW;   // 1 KB loads per wave and stage
+  static constexpr int LPS = XL + WL;
+  static constexpr int kXElems = BM * kBK, kWElems = BN * kBK;
+  static constexpr int kSlot = kXElems + kWElems;
+  static constexpr int WC = BN / 8;       // 16-byte chunks per W row
+  static_assert(BN >= 64 && BN <= 512 && XL >= 1 && WL >= 1, "loads per wave");
+  static_assert((S - 2) * LPS <= 63, "vmcnt range");
+  // chunk swizzle of W row k: the 4 rows x 64 bytes one transposing read
+  // touches fall on distinct banks
+  static __device__ __forceinline__ int wswz(int k) { return BN == 64 ? 4 * ((k >> 1) & 1) : 4 * (k & 3); }
+};
+
+// a lane's global addresses for its loads of a tile's stages
+template <class C>
+struct SmallCtx {
+  i32x4 ra, rb;
+  uint32_t xo[C::XL], wo[C::WL];
+  int xk[C::XL], wk[C::WL];
+  uint32_t lds;
+};
+
+// Stage kt's loads into ring slot `slot`.  Stages past the reduction are
+// issued as well (out of range: zeros, no memory request), so that every
+// stage adds LPS to vmcnt.
+template <class C, class Args>
+__device__ __forceinline__ void small_issue(const Args& a, const SmallCtx<C>& t, int kt, int slot,
+                                            int wave) {
+  const int k0 = kt * kBK;
+  const uint32_t base = t.lds + (uint32_t)slot * (C::kSlot * 2);
+#pragma unroll
+  for (int q = 0; q < C::WL; ++q) {
+    const int kw = k0 + t.wk[q];
+    dma16(t.rb, kw < gemm_k(a) ? t.wo[q] + 2u * (uint32_t)k0 * (uint32_t)gemm_ldb(a) : kOutOfRange,
+          base + (uint32_t)(C::kXElems * 2 + (C::WL * wave + q) * 1024));
+  }
+#pragma unroll
+  for (int q = 0; q < C::XL; ++q) {
+    const int kx = k0 + t.xk[q];
+    dma16(t.ra, kx < gemm_k(a) ? t.xo[q] + 2u * (uint32_t)k0 : kOutOfRange,
+          base + (uint32_t)((C::XL * wave + q) * 1024));
+  }
+}
+
+// byte offset of the A row `row` of the tile at r0
+__device__ __forceinline__ uint32_t small_a_off(const KArgs& a, int r0, int row) {
+  return (uint32_t)row * (uint32_t)a.I * 2u;
+}
+__device__ __forceinline__ uint32_t small_a_off(const G1Args& a, int r0, int row) {
+  int t = a.token_ids[(long long)r0 + row];
+  if (t < 0 || t >= a.T) {
+    __hip_atomic_fetch_or(a.status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    t = 0;
+  }
+  return (uint32_t)t * (uint32_t)a.H * 2u;
+}
+__device__ __forceinline__ int small_n(const KArgs& a) { return a.H; }
+__device__ __forceinline__ int small_n(const G1Args& a) { return 2 * a.I; }
+
+struct SmallUnit {
+  int e, r0, rows_valid, nt;
+  bool ok;
+};
+
+// This workgroup's unit (expert -> n-tile -> m-tile; consecutive units of an
+// XCD are neighbours), by each wave for itself.
+template <int BM>
+__device__ __forceinline__ SmallUnit small_unit(const int32_t* offsets, long long rows, int E,
+                                                int NT, uint32_t* status, int* rows_dev) {
+  const int lane = threadIdx.x & 63;
+  int s = 0, cnt = 0, nm = 0, v = 0;
+  bool bad = false;
+  auto scan = [&](int e0) {   // lane's expert e0 + lane; v: inclusive m-tile prefix in the chunk
+    const int e = e0 + lane;
+    s = cnt = 0;
+    if (e < E) {
+      long long b = offsets[e], en = offsets[e + 1];
+      if ((e == 0 && b != 0) || en < b || en > rows) bad = true;
+      b = b < 0 ? 0 : (b > rows ? rows : b);
+      en = en < b ? b : (en > rows ? rows : en);
+      s = (int)b;
+      cnt = (int)(en - b);
+    }
+    nm = (cnt + BM - 1) / BM;
+    v = nm;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int u = __shfl_up(v, d);
+      if (lane >= d) v += u;
+    }
+  };
+  int total = 0, last = 0;
+  for (int e0 = 0; e0 < E; e0 += 64) {
+    scan(e0);
+    total += __builtin_amdgcn_readlane(v, 63);
+    last = __builtin_amdgcn_readlane(s + cnt, (E - 1) & 63);
+  }
+  *rows_dev = last;
+  if (bad && blockIdx.x == 0)
+    __hip_atomic_fetch_or(status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  SmallUnit u = {0, 0, 0, 0, false};
+  const int b = blockIdx.x;
+  const long long units = (long long)total * NT;
+  const long long chunk = (units + 7) >> 3;
+  const long long unit = (long long)(b & 7) * chunk + (b >> 3);
+  u.ok = (b >> 3) < chunk && unit < units;
+  if (!u.ok) return u;
+  const int mt = (int)(unit / NT);
+  int carry = 0, e0 = 0;
+  if (E > 64) {
+    for (;; e0 += 64) {
+      scan(e0);
+      const int sum = __builtin_amdgcn_readlane(v, 63);
+      if (mt < carry + sum) break;
+      carry += sum;
+    }
+  }
+  // the lane whose expert holds m-tile mt: the first with prefix end > mt
+  const int j = (int)__builtin_ctzll(__ballot(carry + v > mt));
+  u.e = e0 + j;
+  const int first = carry + __builtin_amdgcn_readlane(v - nm, j);
+  const int n_m = __builtin_amdgcn_readlane(nm, j);
+  const int within = (int)(unit - (long long)first * NT);
+  u.nt = within / n_m;
+  const int mi = within - u.nt * n_m;
+  u.r0 = __builtin_amdgcn_readlane(s, j) + mi * BM;
+  u.rows_valid = min(BM, __builtin_amdgcn_readlane(cnt, j) - mi * BM);
+  return u;
+}
+
+// The tile's Y rows, through each wave's own part of the ring to 64- or
+// 128-byte row pieces (as the persistent kernel's epilogue).
+template <class C>
+__device__ __forceinline__ void small_store(const KArgs& a, f32x16 (&acc)[C::NB][C::MB],
+                                            uint16_t* smem, const SmallUnit& u, int wave, int lane,
+                                            int wn0, int wm0, int n0, int cols_valid) {
+  constexpr int EC = C::WN / 8;
+  constexpr int kPerLine = 256 / (2 * C::WN);
+  const int h = lane >> 5;
+  __attribute__((address_space(3))) uint16_t* ep =
+      (__attribute__((address_space(3))) uint16_t*)(uintptr_t)lds_addr(smem) + wave * (C::WM * C::WN);
+#pragma unroll
+  for (int mb = 0; mb < C::MB; ++mb) {
+    const int row = 32 * mb + (lane & 31);
+    const int sw = (row / kPerLine) % EC;
+#pragma unroll
+    for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        bf16x8 v;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = (__bf16)acc[nb][mb][8 * c + i];
+        const int chunk = 4 * nb + 2 * c + h;
+        *(__attribute__((address_space(3))) bf16x8*)(ep + row * C::WN + ((chunk ^ sw) << 3)) = v;
+      }
+  }
+  const int j = lane % EC;
+  const int n = wn0 + 8 * j;
+#pragma unroll
+  for (int it = 0; it < C::WM * EC / 64; ++it) {
+    const int row = it * (64 / EC) + lane / EC;
+    const int sw = (row / kPerLine) % EC;
+    const bf16x8 v =
+        *(const __attribute__((address_space(3))) bf16x8*)(ep + row * C::WN + ((j ^ sw) << 3));
+    if (n < cols_valid && wm0 + row < u.rows_valid)
+      *(u32x4*)(a.Y + (size_t)(u.r0 + wm0 + row) * a.ypitch + n0 + n) = __builtin_bit_cast(u32x4, v);
+  }
+}
+
+// The up-projection's outputs: a lane holds the gate (accumulators 0..7) and
+// the up (8..15) values of the same 8 outputs.
+template <class C>
+__device__ __forceinline__ void small_store(const G1Args& a, f32x16 (&acc)[C::NB][C::MB],
+                                            uint16_t* smem, const SmallUnit& u, int wave, int lane,
+                                            int wn0, int wm0, int n0, int cols_valid) {
+  const int h = lane >> 5;
+#pragma unroll
+  for (int mb = 0; mb < C::MB; ++mb) {
+    const int row = wm0 + 32 * mb + (lane & 31);
+#pragma unroll
+    for (int nb = 0; nb < C::NB; ++nb) {
+      bf16x8 v;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float g = acc[nb][mb][i];
+        const float w = acc[nb][mb][8 + i];
+        v[i] = (__bf16)(g / (1.f + __expf(-g)) * w);
+      }
+      if (wn0 + 32 * nb < cols_valid && row < u.rows_valid)
+        *(u32x4*)(a.xout + (size_t)(u.r0 + row) * a.I + (n0 + wn0) / 2 + 16 * nb + 8 * h) =
+            __builtin_bit_cast(u32x4, v);
+    }
+  }
+}
+
+// A workgroup's share of the token -> rows inverse map, built beside its
+// unit: the token ids load with the expert offsets, the counters' atomics go
+// out before the operand loads, and their results are used after the unit.
+template <int kThr>
+struct RowShare {
+  u64 epoch = 0, cnt_epoch = 0, slot_word = 0;
+  int per = 0, row = -1, tok = -1;
+
+  __device__ __forceinline__ void load(const KArgs& a) {
+    epoch = launch_epoch(a);
+    cnt_epoch = (epoch & ((1ull << (64 - kCntBits)) - 1)) << kCntBits;
+    per = (int)((a.rows + gridDim.x - 1) / gridDim.x);
+    const long long r = (long long)blockIdx.x * per + threadIdx.x;
+    if ((int)threadIdx.x < per && r < a.rows) {
+      row = (int)r;
+      tok = a.token_ids[r];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+      __hip_atomic_store(a.map_epoch, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ bool valid(const KArgs& a, int t) {
+    if (t >= 0 && t < a.T) return true;
+    __hip_atomic_fetch_or(a.status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return false;
+  }
+  __device__ __forceinline__ u64 take(const KArgs& a, int t) {
+    __hip_atomic_fetch_max(&a.tok_cnt[t], cnt_epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_fetch_add(&a.tok_cnt[t], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void place(const KArgs& a, int r, int t, u64 old) {
+    const uint32_t slot =
+        (old & ~kCntMask) == cnt_epoch ? (uint32_t)(old & kCntMask) : 0xffffffffu;
+    if (slot >= (uint32_t)a.topk)
+      __hip_atomic_fetch_or(a.status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+      a.inv[(long long)t * a.topk + slot] = (int32_t)r;
+  }
+  __device__ __forceinline__ void claim(const KArgs& a, int rows_dev) {
+    if (row >= rows_dev) row = -1;
+    if (row >= 0 && !valid(a, tok)) row = -1;
+    // more rows than threads in the share: the rest at once
+    for (int i = threadIdx.x + kThr; i < per; i += kThr) {
+      const long long r = (long long)blockIdx.x * per + i;
+      if (r >= rows_dev) break;
+      const int t = a.token_ids[r];
+      if (valid(a, t)) place(a, (int)r, t, take(a, t));
+    }
+    if (row >= 0) slot_word = take(a, tok);
+  }
+  __device__ __forceinline__ void finish(const KArgs& a) {
+    if (row >= 0) place(a, row, tok, slot_word);
+  }
+  // the up-projection needs no inverse map
+  __device__ __forceinline__ void load(const G1Args&) {}
+  __device__ __forceinline__ void claim(const G1Args&, int) {}
+  __device__ __forceinline__ void finish(const G1Args&) {}
+};
+
+template <class C, class Args>
+__global__ void __launch_bounds__(C::kThr) small_gemm_kernel(Args a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[C::S * C::kSlot];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int N = small_n(a);
+  const int NT = (N + C::BN - 1) / C::BN;
+  RowShare<C::kThr> share;
+  share.load(a);
+  int rows_dev;
+  const SmallUnit u = small_unit<C::BM>(a.offsets, a.rows, a.E, NT, a.status, &rows_dev);
+  share.claim(a, rows_dev);
+  if (u.ok) {
+    const int n0 = u.nt * C::BN;
+    const int cols_valid = min(C::BN, N - n0);
+    SmallCtx<C> t;
+    t.lds = lds_addr(smem);
+    const int ldb = gemm_ldb(a);
+    t.rb = buffer_rsrc(gemm_b(a, u.e) + n0, ((long long)gemm_k(a) * ldb - n0) * 2);
+    t.ra = buffer_rsrc(gemm_a_base(a, u.r0), gemm_a_bytes(a, u.r0));
+#pragma unroll
+    for (int q = 0; q < C::WL; ++q) {
+      const int i = C::WL * wave + q;
+      const int flat = 64 * i + lane;   // 16-byte chunk of the stage
+      const int krow = flat / C::WC;
+      const int wc = (flat % C::WC) ^ C::wswz(krow);
+      t.wk[q] = krow;
+      t.wo[q] = 8 * wc < cols_valid ? 16u * (uint32_t)wc + 2u * (uint32_t)krow * (uint32_t)ldb
+                                    : kOutOfRange;
+    }
+#pragma unroll
+    for (int q = 0; q < C::XL; ++q) {
+      const int row = 8 * (C::XL * wave + q) + lane / 8;
+      const int lc = (lane % 8) ^ ((row / kXRowsPerLine) % kXChunks);
+      t.xk[q] = 8 * lc;
+      t.xo[q] = row < u.rows_valid ? small_a_off(a, u.r0, row) + 16u * (uint32_t)lc : kOutOfRange;
+    }
+    const int wn0 = (wave % C::WNW) * C::WN;
+    const int wm0 = (wave / C::WNW) * C::WM;
+    int offA[C::NB];
+    {
+      const int j = lane & 15;
+      const int krow = 8 * (lane >> 5) + (j >> 2);
+      const int uu = j & 3;
+      const int rg = (lane >> 4) & 1;
+#pragma unroll
+      for (int nb = 0; nb < C::NB; ++nb) {
+        const int col = wn0 + 32 * nb + 16 * rg + 8 * (uu & 1) + 4 * (uu >> 1);
+        offA[nb] = C::kXElems + krow * C::BN + (((col >> 3) ^ C::wswz(krow)) << 3) + (col & 7);
+      }
+    }
+    int offB[kKS];
+    {
+      const int m = wm0 + (lane & 31);
+#pragma unroll
+      for (int ks = 0; ks < kKS; ++ks) {
+        const int c = 2 * ks + (lane >> 5);
+        offB[ks] = m * kBK + ((c ^ ((m / kXRowsPerLine) % kXChunks)) << 3);
+      }
+    }
+    const int nk = (gemm_k(a) + kBK - 1) / kBK;
+#pragma unroll
+    for (int s = 0; s + 1 < C::S; ++s) small_issue<C>(a, t, s, s, wave);
+    f32x16 acc[C::NB][C::MB];
+#pragma unroll
+    for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+      for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[nb][mb][i] = 0.f;
+    int slot = 0, fill = C::S - 1;
+    for (int kt = 0; kt < nk; ++kt) {
+      waitcnt_vm<(C::S - 2) * C::LPS>();
+      block_barrier();
+      small_issue<C>(a, t, kt + C::S - 1, fill, wave);
+      lds_u16* st = (lds_u16*)(uintptr_t)(t.lds + (uint32_t)slot * (C::kSlot * 2));
+      auto frags = [&](int ks, bf16x8 (&af)[C::NB], bf16x8 (&bm)[C::MB]) {
+#pragma unroll
+        for (int nb = 0; nb < C::NB; ++nb) {
+          const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (lds_i16x4*)(st + offA[nb] + ks * 16 * C::BN));
+          const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (lds_i16x4*)(st + offA[nb] + ks * 16 * C::BN + 4 * C::BN));
+          const i16x8 w = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+          af[nb] = __builtin_bit_cast(bf16x8, w);
+        }
+#pragma unroll
+        for (int mb = 0; mb < C::MB; ++mb)
+          bm[mb] = *(const __attribute__((address_space(3))) bf16x8*)(st + offB[ks] + mb * 32 * kBK);
+      };
+      auto mfmas = [&](const bf16x8 (&af)[C::NB], const bf16x8 (&bm)[C::MB]) {
+#pragma unroll
+        for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+          for (int mb = 0; mb < C::MB; ++mb)
+            acc[nb][mb] =
+                __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[nb], bm[mb], acc[nb][mb], 0, 0, 0);
+      };
+      // the next step's fragments are read ahead of this step's MFMAs
+      bf16x8 af[2][C::NB], bm[2][C::MB];
+      frags(0, af[0], bm[0]);
+#pragma unroll
+      for (int ks = 0; ks < kKS; ++ks) {
+        if (ks + 1 < kKS) frags(ks + 1, af[(ks + 1) & 1], bm[(ks + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        mfmas(af[ks & 1], bm[ks & 1]);
+      }
+      slot = slot + 1 == C::S ? 0 : slot + 1;
+      fill = fill + 1 == C::S ? 0 : fill + 1;
+    }
+    waitcnt_vm<0>();   // no load may land in the ring under the epilogue
+    block_barrier();
+    small_store<C>(a, acc, smem, u, wave, lane, wn0, wm0, n0, cols_valid);
+  }
+  share.finish(a);
+}
+
+// out[t, :] for every token: one wave per token and 256 columns.  The
+// token's count, its rows (in inverse-map order, sorted by rank across the
+// lanes) and then its gates and Y rows are two dependent round trips; with
+// many tokens it is bound by the Y rows read and the output written (T =
+// 1024, H = 2048, top-6: 34 MB in 8.0 us).  The first launch built the
+// inverse map under launch epoch *map_epoch; storing that as the workspace's
+// completed epoch ends the launch pair (only the first launch reads it).
+constexpr int kSmallCombineWaves = 4;
+__global__ void __launch_bounds__(kSmallCombineWaves * 64) small_combine_kernel(KArgs a) {
+  const int lane = threadIdx.x & 63;
+  const u64 epoch =
+      __hip_atomic_load(a.map_epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    __hip_atomic_store(a.epoch_word, (uint32_t)(epoch + 1) == 0 ? epoch + 1 : epoch,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int cbs = (a.H + 255) / 256;
+  const long long unit = (long long)blockIdx.x * kSmallCombineWaves +
+                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int t = (int)(unit / cbs);
+  if (t >= a.T) return;
+  const int col = (int)(unit - (long long)t * cbs) * 256 + 4 * lane;
+  const u64 cnt_epoch = (epoch & ((1ull << (64 - kCntBits)) - 1)) << kCntBits;
+  const int K = a.topk;
+  const uint32_t have = epoch_count(a.tok_cnt[t], cnt_epoch);
+  int r = lane < K ? a.inv[(long long)t * K + lane] : 0;
+  const int n = __builtin_amdgcn_readfirstlane((int)(have < (uint32_t)K ? have : (uint32_t)K));
+  float g = 0.f;
+  if (lane < n) g = a.gate_w[r];
+  // ascending row order: lane q < n sends its row to the lane of its rank
+  int rank = lane;
+  if (lane < n) rank = 0;
+  for (int q = 0; q < n; ++q) {
+    const int rq = __builtin_amdgcn_readlane(r, q);
+    if (lane < n) rank += rq < r;
+  }
+  const int rs = __builtin_amdgcn_ds_permute(4 * rank, r);
+  const int gs = __builtin_amdgcn_ds_permute(4 * rank, __float_as_int(g));
+  const bool ok = col < a.H;
+  const uint16_t* y = a.Y + (ok ? col : 0);
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int j0 = 0; j0 < n; j0 += 8) {
+    u32x2 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int j = j0 + q < n ? j0 + q : n - 1;
+      v[q] = *(const u32x2*)(y + (size_t)__builtin_amdgcn_readlane(rs, j) * a.ypitch);
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (j0 + q < n) fma4(acc, __int_as_float(__builtin_amdgcn_readlane(gs, j0 + q)), v[q]);
+  }
+  if (ok) *(f32x4*)(a.out + (size_t)t * a.H + col) = f32x4{acc[0], acc[1], acc[2], acc[3]};
+}

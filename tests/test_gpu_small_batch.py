@@ -1,0 +1,90 @@
+"""The small-batch launches (two launches without waits, four tile shapes)
+against the CPU oracle, and bitwise against the persistent kernel, which an
+explicit consumer count always takes."""
+import numpy as np
+import pytest
+
+from oracle import combine as oc
+from workloads import custom, explicit
+
+pytestmark = pytest.mark.gpu
+
+
+def _edge_counts(counts, T, H, I, seed):
+    """Workload whose expert e owns exactly counts[e] rows."""
+    rng = np.random.default_rng(seed)
+    sel = [[] for _ in range(T)]
+    for e, c in enumerate(counts):
+        for t in rng.choice(T, size=c, replace=False):
+            sel[t].append(e)
+    gates = [rng.random(len(s)).astype(np.float32) + 0.1 for s in sel]
+    return explicit(T=T, H=H, I=I, E=len(counts), sel=sel, gates=gates, L=1, seed=seed)
+
+
+CASES = {
+    # 64 x 64 tiles: one token; a reduction of 40 (not a multiple of 16)
+    "one_token": lambda: custom(T=1, H=2048, I=704, E=32, topk=6, L=2, seed=3),
+    "k_tail": lambda: custom(T=19, H=264, I=40, E=5, topk=2, L=1, seed=4),
+    # 64 x 128 tiles, deep ring (256..511 tiles) and shallow (512 and more)
+    "deep_ring": lambda: custom(T=64, H=1024, I=72, E=32, topk=8, L=1, seed=5),
+    "many_tiles": lambda: custom(T=128, H=2056, I=104, E=64, topk=4, L=1,
+                                 routing=("zipf", 1.0), seed=6),
+    # 128 x 128 tiles
+    "wide": lambda: custom(T=515, H=4096, I=64, E=8, topk=2, L=2, seed=7),
+    # more experts than a wave has lanes, most of them without rows
+    "experts_200": lambda: custom(T=40, H=512, I=64, E=200, topk=3, L=1, seed=8),
+    # expert row counts at the edges of the 64- and 128-row tiles, empty experts
+    "edges_64": lambda: _edge_counts([63, 0, 64, 65, 1, 0, 33], 130, 520, 136, 9),
+    "edges_128": lambda: _edge_counts([127, 128, 0, 129, 255, 256, 257, 1], 300, 4104, 24, 10),
+    "topk_64": lambda: custom(T=70, H=256, I=32, E=64, topk=64, L=1, seed=11),
+}
+
+
+def _bits(a):
+    return np.ascontiguousarray(a).view(np.uint32)
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_small_batch_matches_oracle_and_persistent_kernel(gpu_lib, name):
+    import gpu_util
+    w = CASES[name]()
+    print(f"{name}: T={w.T} H={w.H} I={w.I} E={w.E} k={w.topk} rows={w.Mtot}", flush=True)
+    ref = oc.combine_reference(w.x_perm, w.w2, w.expert_offsets, w.token_ids, w.gate_w, w.T)
+    dev = gpu_util.to_device(w)
+    got, _, ws = gpu_util.run(w, C=0, dev=dev)
+    assert oc.rel_l2(got, ref) <= oc.REL_L2_TOL
+    assert oc.max_abs_ratio(got, ref) <= oc.MAX_ABS_TOL
+    # both paths in turn on one workspace (they share its epoch and counters)
+    for C in (3, 0, -1, 3, -1, 0):
+        again, _, ws = gpu_util.run(w, C=C, dev=dev, workspace=ws)
+        assert np.array_equal(_bits(again), _bits(got)), C
+    bands, _, _ = gpu_util.run(w, C=0, dev=dev, mode=2)
+    assert np.array_equal(_bits(bands), _bits(got))
+
+
+def test_small_batch_unsorted_rows_and_no_rows(gpu_lib):
+    """Rows in any order inside an expert, tokens without rows, and a call
+    whose experts hold no rows at all."""
+    import torch
+
+    import gpu_util
+    from paper_2609_07536_amd import binding as B
+    w = custom(T=90, H=512, I=96, E=6, topk=3, L=1, seed=12)
+    rng = np.random.default_rng(1)
+    for e in range(w.E):
+        a, b = w.expert_offsets[e], w.expert_offsets[e + 1]
+        p = a + rng.permutation(b - a)
+        w.x_perm[a:b], w.token_ids[a:b] = w.x_perm[p], w.token_ids[p]
+        w.gate_w[a:b] = w.gate_w[p]
+    ref = oc.combine_reference(w.x_perm, w.w2, w.expert_offsets, w.token_ids, w.gate_w, w.T)
+    dev = gpu_util.to_device(w)
+    got, _, ws = gpu_util.run(w, C=0, dev=dev)
+    assert oc.rel_l2(got, ref) <= oc.REL_L2_TOL
+    persistent, _, _ = gpu_util.run(w, C=3, dev=dev, workspace=ws)
+    assert np.array_equal(_bits(persistent), _bits(got))
+    x, w2, off, tid, g = dev
+    out = torch.full((w.T, w.H), float("nan"), device="cuda")
+    B.combine(x, w2, torch.zeros_like(off), tid, g, T=w.T, topk=w.topk, num_consumers=0, out=out,
+              workspace=ws)
+    torch.cuda.synchronize()
+    assert (out == 0).all()
