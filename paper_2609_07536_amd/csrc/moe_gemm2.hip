@@ -2328,11 +2328,11 @@ hipError_t launch_small_gemm(const Args& a, int cus, hipStream_t s) {
                          : launch_small_tile<SmallTile64>(a, s);
 }
 
-// 256 x 256 tiles of an average routing (half a tile's rows of padding per
+// tile x tile tiles of an average routing (half a tile's rows of padding per
 // expert), over N columns.
-long long expected_tiles(long long rows, int E, int N) {
+long long expected_tiles(long long rows, int E, int N, int tile = kBN) {
   const long long n = E < rows ? E : rows;
-  return (2 * rows + kBM * n) * ((N + kBN - 1) / kBN) / (2 * kBM);
+  return (2 * rows + tile * n) * ((N + tile - 1) / tile) / (2 * tile);
 }
 
 // The stage runs as small tiles up to about four 256 x 256 tiles per CU:
@@ -2343,6 +2343,19 @@ long long expected_tiles(long long rows, int E, int N) {
 // 4.5 (H = 2048, I = 704, E = 30, top-4, T = 8192) 155 / 178.
 bool small_stage(long long rows, int E, int H, int cus) {
   return expected_tiles(rows, E, H) <= 4LL * cus;
+}
+
+// The up-projection runs as small tiles where its persistent kernel, which
+// takes whole rounds of one 256 x 256 tile per CU, would take longer: in such
+// rounds the small tiles take 0.35 + 1.25 per CU's worth of 128 x 128
+// quadruples, fitted to (us, persistent / small): H = 2048, I = 704, E = 32,
+// T = 512 48 / 33.5, 1024 (one full round) 56 / 58, 2048 (1.5 rounds) 104 /
+// 90, 4096 (2.6) 159 / 158, 8192 (4.5) 274 / 318; H = 1024, I = 512, E = 32,
+// T = 2048 (1.25) 61 / 51, 8192 (4.25) 154 / 164; H = 1352, I = 336, E = 11,
+// T = 4096 (0.6) 43 / 49.
+bool small_up_projection(long long rows, int E, int N, int cus) {
+  const long long rounds = (expected_tiles(rows, E, N) + cus - 1) / cus;
+  return 28LL * cus + 25 * expected_tiles(rows, E, N, 128) < 80LL * cus * rounds;
 }
 
 // `layout_slot`: where the workspace's last layout is kept when the
@@ -2705,6 +2718,9 @@ int launch_gemm1(const void* hidden, const void* w1, const int32_t* expert_offse
   a.E = wl->E;
   a.ntps = (2 * wl->I + kBN - 1) / kBN;
   a.nsplit = 2 * wl->I;
+  if (small_up_projection(rows, wl->E, a.nsplit, d.cus))
+    return launch_small_gemm(a, d.cus, static_cast<hipStream_t>(stream)) == hipSuccess
+               ? MOE_OK : MOE_ERR_HIP;
   const int grid = d.occ * d.cus;
   hipLaunchKernelGGL(moe_gemm1_swiglu_kernel, dim3(grid), dim3(kThreads), 0,
                      static_cast<hipStream_t>(stream), a);

@@ -88,3 +88,41 @@ def test_small_batch_unsorted_rows_and_no_rows(gpu_lib):
               workspace=ws)
     torch.cuda.synchronize()
     assert (out == 0).all()
+
+
+# the up-projection: E, H, I, T, topk for each tile shape, edges of its rows
+# and columns (2I = 96, 160, 1344 packed columns), a gather of repeated tokens
+UP = {
+    "one_token": (32, 2048, 704, 1, 6),
+    "odd": (11, 1352, 336, 130, 3),
+    "k_tail": (5, 264, 48, 40, 2),
+    "deep_ring": (32, 520, 512, 64, 8),
+    "many_tiles": (64, 264, 672, 128, 4),
+    "wide": (8, 128, 2048, 515, 2),
+    "experts_200": (200, 256, 80, 60, 3),
+}
+
+
+@pytest.mark.parametrize("name", list(UP))
+def test_small_batch_up_projection(gpu_lib, name):
+    """Against fp32 torch on the device: one bf16 rounding of the activation
+    (2^-9 of its value) on top of fp32 sums of H products."""
+    import torch
+
+    import gpu_util
+    from paper_2609_07536_amd import binding as B
+    E, H, I, T, k = UP[name]
+    print(f"{name}: E={E} H={H} I={I} T={T} k={k}", flush=True)
+    w = custom(T=T, H=H, I=I, E=E, topk=k, L=1, routing=("zipf", 1.0), seed=13)
+    _, _, off, tid, _ = gpu_util.to_device(w)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    hidden = torch.randn((T, H), generator=gen, device="cuda").bfloat16()
+    w1 = (torch.randn((E, H, 2 * I), generator=gen, device="cuda") / H ** 0.5).bfloat16()
+    got = B.gemm1_swiglu(hidden, B.pack_w1(w1), off, tid, k, w.Mtot)
+    ref = torch.empty((w.Mtot, I), device="cuda")
+    for e in range(E):
+        a, b = int(w.expert_offsets[e]), int(w.expert_offsets[e + 1])
+        h = hidden[tid[a:b].long()].float() @ w1[e].float()
+        ref[a:b] = torch.nn.functional.silu(h[:, :I]) * h[:, I:]
+    # fp32 sums of up to 2048 products of unit variance: about 1e-6 each way
+    assert (got.float() - ref).abs().le(2 ** -8 * ref.abs() + 2e-4).all()
