@@ -19,6 +19,12 @@
  * selector below evaluates its wave-quantized makespan model (Method,
  * "Wave-Quantized Pipeline Model" and Algorithm 1) to choose it.
  *
+ * Calls that ask for no dedicated consumers (num_consumers 0 or -1, modes 0
+ * and 2, no trace) run instead as two launches without flags or waits: a
+ * grouped GEMM whose tile sizes follow the batch, then the combine.  Both
+ * ways compute every output element by the same operations in the same
+ * order, so their results are bitwise equal.
+ *
  * Conventions for every function:
  *   - all functions are extern "C"; none throws, aborts or prints;
  *   - a negative return value is a moe_status_t error; 0 or a documented
@@ -305,12 +311,16 @@ int moe_gemm2_workspace_init(void* workspace, size_t workspace_bytes, void* stre
  *   wl              dimensions (+ optional host counts for the selector)
  *   num_consumers   >= 1: that many consumer workgroups (an explicit choice
  *                   wins, Method "System Integration and Correctness");
- *                   0: no dedicated consumers, every workgroup computes its
- *                   tiles and then takes consumer tasks;
- *                   -1: chosen by moe_select_partition with
+ *                   0: no dedicated consumers: the GEMM's launch, then the
+ *                   combine's (traced calls, and calls with the debugging
+ *                   variables below set: one launch whose workgroups compute
+ *                   their tiles and then take consumer tasks);
+ *                   -1: the value returned is chosen by moe_select_partition with
  *                   moe_gemm2_launch_params(device, 0, wl), unless the
  *                   environment sets
- *                   MOE_GEMM2_SELECTOR=0, which restores a fixed C = 8
+ *                   MOE_GEMM2_SELECTOR=0, which restores a fixed C = 8; the
+ *                   call runs as with 0 (a traced or debugged call, and the
+ *                   atomic scatter, with the C returned)
  *   workspace       device memory of at least moe_gemm2_workspace_size(wl)
  *                   bytes, 256-byte aligned, zeroed once by
  *                   moe_gemm2_workspace_init; calls that may overlap in
@@ -332,7 +342,8 @@ int moe_gemm2_workspace_init(void* workspace, size_t workspace_bytes, void* stre
  * within 2 GiB) (else MOE_ERR_UNSUPPORTED).
  * Values inside device arrays are checked by the kernel, which skips bad
  * entries and records MOE_ERR_BAD_ROUTING for moe_gemm2_status.
- * Launches on other streams may share the GPU: compute workgroups never
+ * Launches on other streams may share the GPU: the two launches of a call
+ * without dedicated consumers never wait; in the persistent kernel compute workgroups never
  * wait while they hold tiles, with C = 0 a workgroup waits on other
  * workgroups' tiles only once its whole grid has started, and dedicated
  * consumers (C >= 1) wait only on compute workgroups, which never wait; so
@@ -341,8 +352,8 @@ int moe_gemm2_workspace_init(void* workspace, size_t workspace_bytes, void* stre
  * MOE_ERR_TIMEOUT).  Debugging aid: MOE_GEMM2_DEBUG_PUBLISH_DELAY="m:t"
  * makes the compute workgroups whose index is a multiple of m hold each
  * split publish back by t ticks of the 100 MHz clock (t <= 10^6).
- * Returns the number of consumer workgroups launched (>= 0) or a negative
- * status (host-side validation and launch errors only). */
+ * Returns the number of consumer workgroups asked for or chosen (>= 0) or a
+ * negative status (host-side validation and launch errors only). */
 int moe_gemm2_combine(const void* x_perm, const void* w2, const int32_t* expert_offsets,
                       const int32_t* token_ids, const float* gate_w, float* out,
                       const moe_workload_t* wl, int32_t num_consumers,
@@ -496,8 +507,8 @@ int moe_gemm1_pack_weights(const void* w_gate_up, void* w1_packed, int32_t E, in
  *   workspace       a moe_gemm2 workspace (at least 512 bytes, 256-byte
  *                   aligned, zeroed once by moe_gemm2_workspace_init): only
  *                   its status word is used
- * One persistent launch, every workgroup computing 256 x 256 tiles of the
- * packed columns.  Supported: H % 8 == 0, I % 16 == 0, 1 <= E <= 1024,
+ * One launch, its tiles (64 x 64 to 256 x 256 of the packed columns) chosen
+ * by the batch.  Supported: H % 8 == 0, I % 16 == 0, 1 <= E <= 1024,
  * 1 <= topk <= 64, 2 T H < 2^31 and 4 H I < 2^31 (hidden and one expert's
  * W1 slice within 2 GiB) (else MOE_ERR_UNSUPPORTED).  Returns 0 or a negative
  * status (host-side validation and launch errors). */

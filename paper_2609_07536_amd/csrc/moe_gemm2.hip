@@ -115,6 +115,7 @@ struct KArgs {
   u64* map_epoch;             // small batches: the epoch the first launch built the inverse map with
   uint32_t* done_ctr;         // workgroups of this launch that have finished
   uint32_t* start_ctr;        // workgroups of this launch that have started
+  int y_keep;                 // Y stores without the non-temporal bit
   int delay_mod;              // debug: compute workgroups c % delay_mod == 0 delay
   long long delay_ticks;      //   each split publish by delay_ticks (100 MHz), else 0
   uint32_t* task_ctr;         // [kMaxSplits]: next consumer task of each split (reset by
@@ -137,7 +138,8 @@ struct G1Args {
   uint32_t* status;           // [1]
   long long rows;             // capacity of token_ids / xout
   int T, H, I, E;
-  int ntps;                   // n-tiles of the packed 2I columns
+  int ntps;                   // column blocks of the full tiles (set on the device)
+  int P;                      // workgroups on full tiles
   int nsplit;                 // = 2I (one split)
 };
 
@@ -392,8 +394,9 @@ __device__ long long wait_prefix(Smem& sm, uint32_t* flags, long long from, long
 // flagged); overlapping ranges from bad input compute some rows twice (with
 // meaningless values), and a tile count past the workspace's capacity makes
 // the compute workgroups stop (flagged) instead of indexing past it.
+// An expert has (count + pad) / kBM m-tiles.
 template <class Args>
-__device__ void load_experts(Smem& sm, const Args& a) {
+__device__ void load_experts(Smem& sm, const Args& a, int pad = kBM - 1) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -410,7 +413,7 @@ __device__ void load_experts(Smem& sm, const Args& a) {
     en = en < s ? s : (en > a.rows ? a.rows : en);
     sm.start[e] = (int)s;
     sm.count[e] = (int)(en - s);
-    local += (int)((en - s + kBM - 1) / kBM);
+    local += (int)((en - s + pad) / kBM);
   }
   if (bad && a.status)
     __hip_atomic_fetch_or(a.status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -429,7 +432,7 @@ __device__ void load_experts(Smem& sm, const Args& a) {
   int run = before + v - local;
   for (int e = lo; e < hi; ++e) {
     sm.tile_prefix[e] = run;
-    run += (sm.count[e] + kBM - 1) / kBM;
+    run += (sm.count[e] + pad) / kBM;
   }
   if (tid == kThreads - 1) sm.tile_prefix[a.E] = before + v;
   __syncthreads();
@@ -441,12 +444,14 @@ __device__ void load_experts(Smem& sm, const Args& a) {
 // `publish`, the workgroup's share is published at once (release + its
 // workgroup flag); otherwise the caller publishes it later, with its first
 // split's tiles (one L2 write-back for both).
-__device__ void consumer_prologue(const Smem& sm, const KArgs& a, long long rows_dev, bool publish) {
-  const long long stride = (long long)gridDim.x * kThreads;
+// The share is one of `shares` equal ones, by workgroup id.
+__device__ void consumer_prologue(const Smem& sm, const KArgs& a, long long rows_dev, bool publish,
+                                  int shares) {
+  const long long stride = (long long)shares * kThreads;
   if (a.mode == 1) {
     // out as 16-byte words, split into one contiguous range per workgroup
     const long long words = (long long)a.T * a.H / 4;
-    const long long per = (words + gridDim.x - 1) / gridDim.x;
+    const long long per = (words + shares - 1) / shares;
     const long long lo = (long long)blockIdx.x * per;
     const long long hi = min(words, lo + per);
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
@@ -586,6 +591,9 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void* base, long long bytes) 
 // ordered by the explicit vmcnt waits before a publish.
 __device__ __forceinline__ void store16_nt(void* p, u32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+}
+__device__ __forceinline__ void store16(void* p, u32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ void store8(void* p, u64 v) {
   asm volatile("global_store_dwordx2 %0, %1, off\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
@@ -1013,7 +1021,10 @@ __device__ __forceinline__ void epilogue_store(Smem& sm, const KArgs& a, f32x16 
       const bf16x8 v =
           *(const __attribute__((address_space(3))) bf16x8*)(ep + row * kWN + ((j ^ sw) << 3));
       if (n_ok && m < rows_valid)
-        store16_nt(a.Y + (size_t)(r0 + m) * a.ypitch + ti.ny0 + n, __builtin_bit_cast(u32x4, v));
+        if (a.y_keep)
+          store16(a.Y + (size_t)(r0 + m) * a.ypitch + ti.ny0 + n, __builtin_bit_cast(u32x4, v));
+        else
+          store16_nt(a.Y + (size_t)(r0 + m) * a.ypitch + ti.ny0 + n, __builtin_bit_cast(u32x4, v));
     }
   }
 }
@@ -1722,7 +1733,7 @@ __device__ __forceinline__ void fused_body(Smem& sm, const KArgs& a) {
     issue_prologue(a, tctx, nk, 0, wave);
     filled = true;
   }
-  consumer_prologue(sm, a, rows_dev, !defer_inverse);
+  consumer_prologue(sm, a, rows_dev, !defer_inverse, (int)gridDim.x);
 
   if (b >= a.C) {   // compute role
     if (total > a.max_tiles) {  // cannot happen with sanitized offsets; stay in bounds
@@ -1853,33 +1864,7 @@ moe_gemm2_fused(KArgs a) {
   }
 }
 
-// ---- the up-projection stage: grouped GEMM1 + SwiGLU -----------------------------
-// Every workgroup computes: tiles expert -> m-tile -> n-tile of the packed
-// 2I columns, workgroup c (XCD-aware index) taking tiles c, c+P, ...
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-moe_gemm1_swiglu_kernel(G1Args a) {
-  __shared__ Smem sm;
-  load_experts(sm, a);
-  const int m_tiles = sm.tile_prefix[a.E];
-  const int total = m_tiles * a.ntps;
-  const int P = (int)gridDim.x;
-  const int c = compute_index((int)blockIdx.x, 0, P);
-  if (c >= total) return;
-  const int nk = (a.H + kBK - 1) / kBK;
-  bool filled = false;
-  TileCtx tctx;
-  int base = 0;
-  for (int g = c; g < total; g += P) {
-    const bool next = g + P < total;
-    const TileInfo cur = decode_tile(sm, a, total, g);
-    const TileInfo nt = decode_tile(sm, a, total, next ? g + P : g);
-    u64 t_mid[2];
-    compute_tile(sm, a, cur, filled, next, nt, base, t_mid, tctx);
-    base = (base + nk) % kStages;
-    filled = next;
-  }
-}
-
+// ---- the up-projection's weights -------------------------------------------------
 // W1 from [E, H, 2I] (gate columns 0..I-1, up columns I..2I-1) to the
 // packed layout: column 32b + j holds gate column 16b + j and column
 // 32b + 16 + j up column 16b + j (j < 16).
@@ -2289,7 +2274,8 @@ int validate_args(const void* x_perm, const void* w2, const int32_t* expert_offs
   return MOE_OK;
 }
 
-// ---- launches of small and medium batches (small_batch.h) -----------------------
+// ---- launches without dedicated consumers (small_batch.h) -----------------------
+constexpr long long kMaxSmallGrid = 1 << 22;   // times 512 threads: within a launch's 2^32
 template <class C, class Args>
 long long small_units(const Args& a) {
   // the most tiles that `rows` rows in at most min(E, rows) experts make
@@ -2328,6 +2314,24 @@ hipError_t launch_small_gemm(const Args& a, int cus, hipStream_t s) {
                          : launch_small_tile<SmallTile64>(a, s);
 }
 
+template <class Args>
+hipError_t launch_mixed_gemm(Args a, const DevInfo& d, hipStream_t s) {
+  const int N = a.nsplit;
+  a.P = d.occ * d.cus;
+  const long long n = a.E < a.rows ? a.E : a.rows;
+  // the most smaller tiles of any plan: an edge per 256 rows or part of them,
+  // two bottoms (129 rows or more) or one per expert and column block, each
+  // kind rounded to eight
+  const long long edges = mixed_edge(N) ? (a.rows - n) / kBM + n : 0;
+  long long bottoms = n + a.rows / (MixedBottom::BM + 1);
+  if (bottoms > 2 * n) bottoms = 2 * n;
+  bottoms *= (N + kBN - 1) / kBN;
+  long long grid = a.P + (edges + 7) / 8 * 8 + (bottoms + 7) / 8 * 8;
+  if (grid > kMaxSmallGrid) grid = a.P;   // past what a launch can hold: full tiles only
+  hipLaunchKernelGGL((mixed_gemm_kernel<Args>), dim3((unsigned)grid), dim3(kThreads), 0, s, a);
+  return hipGetLastError();
+}
+
 // tile x tile tiles of an average routing (half a tile's rows of padding per
 // expert), over N columns.
 long long expected_tiles(long long rows, int E, int N, int tile = kBN) {
@@ -2335,27 +2339,56 @@ long long expected_tiles(long long rows, int E, int N, int tile = kBN) {
   return (2 * rows + tile * n) * ((N + tile - 1) / tile) / (2 * tile);
 }
 
-// The stage runs as small tiles up to about four 256 x 256 tiles per CU:
-// beyond that the larger tile's lower operand traffic and the combine under
-// the last tiles win.  Measured (us, persistent / small tiles): 3.5 tiles per
-// CU (H = 2048, I = 704, E = 32, T = 4096) 123 / 118, 4.1 (H = 1024, I = 256,
-// T = 8192) 104 / 93, 4.25 (H = 1024, I = 512, E = 32, T = 8192) 132 / 141,
-// 4.5 (H = 2048, I = 704, E = 30, top-4, T = 8192) 155 / 178.
+// The stage's grouped GEMM runs as small tiles up to two 256 x 256 tiles per
+// CU, beyond that as full tiles with smaller ones for the rest.  Measured
+// (us for the stage, small / full): 2.0 tiles per CU (H = 2048, I = 704, E =
+// 32, T = 2048) 68.8 / 70.3, 2.1 (H = 1024, I = 256, T = 4096) 49.2 / 49.0,
+// 2.5 (H = 2048, I = 704, E = 30, top-4, T = 4096) 85.0 / 78.5, 1.1 (H =
+// 1024, I = 512, E = 8, T = 8192) 43.5 / 46.8, 2.1 (T = 16384) 82.6 / 72.8.
 bool small_stage(long long rows, int E, int H, int cus) {
-  return expected_tiles(rows, E, H) <= 4LL * cus;
+  return expected_tiles(rows, E, H) <= 2LL * cus;
 }
 
-// The up-projection runs as small tiles where its persistent kernel, which
-// takes whole rounds of one 256 x 256 tile per CU, would take longer: in such
-// rounds the small tiles take 0.35 + 1.25 per CU's worth of 128 x 128
-// quadruples, fitted to (us, persistent / small): H = 2048, I = 704, E = 32,
-// T = 512 48 / 33.5, 1024 (one full round) 56 / 58, 2048 (1.5 rounds) 104 /
-// 90, 4096 (2.6) 159 / 158, 8192 (4.5) 274 / 318; H = 1024, I = 512, E = 32,
-// T = 2048 (1.25) 61 / 51, 8192 (4.25) 154 / 164; H = 1352, I = 336, E = 11,
-// T = 4096 (0.6) 43 / 49.
+// Y this small stays in the 256 MB Infinity Cache until the combine reads it
+// when it is stored and read without the non-temporal bit; a larger one only
+// pushes the operands out of it.  Measured (us for the stage, ordinary /
+// non-temporal): Y of 33 MB 39.5 / 45.2, 66 MB 81.6 / 87.0, 99 MB 104.3 /
+// 106.3, 136 MB 76 / 79.6, 198 MB 213.5 / 185.0, 396 MB 414 / 357.
+constexpr long long kYKeepBytes = 144LL << 20;
+
+// The second launch: two column blocks of 256 per wave once one block per
+// wave makes 16 waves per CU (T = 1024, H = 2048: 40.9 / 40.3 us for the
+// stage with one / two, T = 16384, top-4: 261 / 258; T = 64: 20.7 / 21.0).
+hipError_t launch_combine(const KArgs& a, int cus, hipStream_t s) {
+  const long long waves = (long long)a.T * ((a.H + 255) / 256);
+  const bool wide = waves >= 16LL * cus;
+  const long long units = wide ? (long long)a.T * ((a.H + 511) / 512) : waves;
+  const long long blocks = (units + kSmallCombineWaves - 1) / kSmallCombineWaves;
+  const dim3 grid((unsigned)(blocks < kMaxSmallGrid ? blocks : kMaxSmallGrid));
+  const dim3 block(kSmallCombineWaves * 64);
+  if (!a.y_keep)
+    hipLaunchKernelGGL((small_combine_kernel<2, true>), grid, block, 0, s, a);
+  else if (wide)
+    hipLaunchKernelGGL((small_combine_kernel<2, false>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((small_combine_kernel<1, false>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
+// The up-projection in 80ths of the time one full tile takes: small tiles
+// 50 while two per CU hold all of them, then 28 + 25 per 128 x 128 tile and
+// CU; full tiles with smaller ones for the rest 82 while one per CU holds
+// them, then 64 + 80 per 256 x 256 tile's work and CU.  Fitted to (us, small
+// / full): H = 2048, I = 704, E = 32, T = 512 33.5 / 53, 1024 60 / 55, 2048
+// 89 / 90, 4096 156 / 148, 8192 312 / 260; H = 1024, I = 512, E = 32, T =
+// 2048 50.6 / 54.1, 4096 88.8 / 87.6; H = 1352, I = 336, E = 11, T = 2048
+// 26.4 / 38.9, 4096 49.6 / 39.6.
 bool small_up_projection(long long rows, int E, int N, int cus) {
-  const long long rounds = (expected_tiles(rows, E, N) + cus - 1) / cus;
-  return 28LL * cus + 25 * expected_tiles(rows, E, N, 128) < 80LL * cus * rounds;
+  const long long units = expected_tiles(rows, E, N, 128);
+  const long long small = units <= 2LL * cus ? 50LL * cus : 28LL * cus + 25 * units;
+  const long long full = expected_tiles(rows, E, N) <= cus
+                             ? 82LL * cus : 64LL * cus + 80 * (rows * N / (kBM * kBN));
+  return small < full;
 }
 
 // `layout_slot`: where the workspace's last layout is kept when the
@@ -2473,6 +2506,7 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
   a.map_epoch = reinterpret_cast<u64*>(ws + L.status + 336);
   a.done_ctr = reinterpret_cast<uint32_t*>(ws + L.status + 328);
   a.start_ctr = reinterpret_cast<uint32_t*>(ws + L.status + 332);
+  a.y_keep = 0;
   a.delay_mod = 1;
   a.delay_ticks = 0;
   if (const char* s = std::getenv("MOE_GEMM2_DEBUG_PUBLISH_DELAY")) {
@@ -2497,22 +2531,16 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
     clear = workspace_needs_clear(workspace, sig);
   }
   if (clear && zero_async(workspace, L.Y, s) != hipSuccess) return MOE_ERR_HIP;
-  // Small and medium batches with no dedicated consumers asked for run as two
-  // launches without waits (the debugging aids act on the persistent
-  // kernel's waits, so they keep it).
-  if (!trace && num_consumers <= 0 && mode != 1 && !wait_env &&
-      small_stage(L.rows, wl->E, wl->H, d.cus)) {
+  // With no dedicated consumers asked for, two launches without waits (the
+  // debugging aids act on the persistent kernel's waits, so they keep it).
+  if (!trace && num_consumers <= 0 && mode != 1 && !wait_env) {
     a.nsplit = wl->H;
     a.ysplit = round_up_line(wl->H);   // one segment; fits the column-split layout
     a.ypitch = a.ysplit + kYPad;
-    hipError_t e = launch_small_gemm(a, d.cus, s);
-    if (e == hipSuccess) {
-      const long long units = (long long)wl->T * ((wl->H + 255) / 256);
-      hipLaunchKernelGGL(small_combine_kernel,
-                         dim3((unsigned)((units + kSmallCombineWaves - 1) / kSmallCombineWaves)),
-                         dim3(kSmallCombineWaves * 64), 0, s, a);
-      e = hipGetLastError();
-    }
+    a.y_keep = L.rows * (long long)a.ypitch * 2 <= kYKeepBytes;
+    hipError_t e = small_stage(L.rows, wl->E, wl->H, d.cus) ? launch_small_gemm(a, d.cus, s)
+                                                           : launch_mixed_gemm(a, d, s);
+    if (e == hipSuccess) e = launch_combine(a, d.cus, s);
     if (e == hipSuccess) return C;
     // the first launch may have run without the second: the workspace's
     // counters are then those of an unfinished epoch, so clear them next time
@@ -2716,15 +2744,12 @@ int launch_gemm1(const void* hidden, const void* w1, const int32_t* expert_offse
   a.H = wl->H;
   a.I = wl->I;
   a.E = wl->E;
-  a.ntps = (2 * wl->I + kBN - 1) / kBN;
   a.nsplit = 2 * wl->I;
-  if (small_up_projection(rows, wl->E, a.nsplit, d.cus))
-    return launch_small_gemm(a, d.cus, static_cast<hipStream_t>(stream)) == hipSuccess
-               ? MOE_OK : MOE_ERR_HIP;
-  const int grid = d.occ * d.cus;
-  hipLaunchKernelGGL(moe_gemm1_swiglu_kernel, dim3(grid), dim3(kThreads), 0,
-                     static_cast<hipStream_t>(stream), a);
-  return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  const hipError_t e = small_up_projection(rows, wl->E, a.nsplit, d.cus)
+                           ? launch_small_gemm(a, d.cus, s)
+                           : launch_mixed_gemm(a, d, s);
+  return e == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
 }  // namespace

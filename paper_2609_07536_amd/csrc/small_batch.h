@@ -94,13 +94,13 @@ __device__ __forceinline__ int small_n(const KArgs& a) { return a.H; }
 __device__ __forceinline__ int small_n(const G1Args& a) { return 2 * a.I; }
 
 struct SmallUnit {
-  int e, r0, rows_valid, nt;
+  int e, r0, rows_valid, n0;
   bool ok;
 };
 
 // This workgroup's unit (expert -> n-tile -> m-tile; consecutive units of an
 // XCD are neighbours), by each wave for itself.
-template <int BM>
+template <int BM, int BN>
 __device__ __forceinline__ SmallUnit small_unit(const int32_t* offsets, long long rows, int E,
                                                 int NT, uint32_t* status, int* rows_dev) {
   const int lane = threadIdx.x & 63;
@@ -157,8 +157,9 @@ __device__ __forceinline__ SmallUnit small_unit(const int32_t* offsets, long lon
   const int first = carry + __builtin_amdgcn_readlane(v - nm, j);
   const int n_m = __builtin_amdgcn_readlane(nm, j);
   const int within = (int)(unit - (long long)first * NT);
-  u.nt = within / n_m;
-  const int mi = within - u.nt * n_m;
+  const int nt = within / n_m;
+  const int mi = within - nt * n_m;
+  u.n0 = nt * BN;
   u.r0 = __builtin_amdgcn_readlane(s, j) + mi * BM;
   u.rows_valid = min(BM, __builtin_amdgcn_readlane(cnt, j) - mi * BM);
   return u;
@@ -287,121 +288,374 @@ struct RowShare {
   __device__ __forceinline__ void finish(const G1Args&) {}
 };
 
+// The unit's tile, by C::kThr threads with the ring at smem.
+template <class C, class Args>
+__device__ __forceinline__ void small_tile(const Args& a, uint16_t* smem, const SmallUnit& u) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n0 = u.n0, N = small_n(a);
+  const int cols_valid = min(C::BN, N - n0);
+  SmallCtx<C> t;
+  t.lds = lds_addr(smem);
+  const int ldb = gemm_ldb(a);
+  t.rb = buffer_rsrc(gemm_b(a, u.e) + n0, ((long long)gemm_k(a) * ldb - n0) * 2);
+  t.ra = buffer_rsrc(gemm_a_base(a, u.r0), gemm_a_bytes(a, u.r0));
+#pragma unroll
+  for (int q = 0; q < C::WL; ++q) {
+    const int i = C::WL * wave + q;
+    const int flat = 64 * i + lane;   // 16-byte chunk of the stage
+    const int krow = flat / C::WC;
+    const int wc = (flat % C::WC) ^ C::wswz(krow);
+    t.wk[q] = krow;
+    t.wo[q] = 8 * wc < cols_valid ? 16u * (uint32_t)wc + 2u * (uint32_t)krow * (uint32_t)ldb
+                                  : kOutOfRange;
+  }
+#pragma unroll
+  for (int q = 0; q < C::XL; ++q) {
+    const int row = 8 * (C::XL * wave + q) + lane / 8;
+    const int lc = (lane % 8) ^ ((row / kXRowsPerLine) % kXChunks);
+    t.xk[q] = 8 * lc;
+    t.xo[q] = row < u.rows_valid ? small_a_off(a, u.r0, row) + 16u * (uint32_t)lc : kOutOfRange;
+  }
+  const int wn0 = (wave % C::WNW) * C::WN;
+  const int wm0 = (wave / C::WNW) * C::WM;
+  int offA[C::NB];
+  {
+    const int j = lane & 15;
+    const int krow = 8 * (lane >> 5) + (j >> 2);
+    const int uu = j & 3;
+    const int rg = (lane >> 4) & 1;
+#pragma unroll
+    for (int nb = 0; nb < C::NB; ++nb) {
+      const int col = wn0 + 32 * nb + 16 * rg + 8 * (uu & 1) + 4 * (uu >> 1);
+      offA[nb] = C::kXElems + krow * C::BN + (((col >> 3) ^ C::wswz(krow)) << 3) + (col & 7);
+    }
+  }
+  int offB[kKS];
+  {
+    const int m = wm0 + (lane & 31);
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) {
+      const int c = 2 * ks + (lane >> 5);
+      offB[ks] = m * kBK + ((c ^ ((m / kXRowsPerLine) % kXChunks)) << 3);
+    }
+  }
+  const int nk = (gemm_k(a) + kBK - 1) / kBK;
+#pragma unroll
+  for (int s = 0; s + 1 < C::S; ++s) small_issue<C>(a, t, s, s, wave);
+  f32x16 acc[C::NB][C::MB];
+#pragma unroll
+  for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+    for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[nb][mb][i] = 0.f;
+  int slot = 0, fill = C::S - 1;
+  for (int kt = 0; kt < nk; ++kt) {
+    waitcnt_vm<(C::S - 2) * C::LPS>();
+    block_barrier();
+    small_issue<C>(a, t, kt + C::S - 1, fill, wave);
+    lds_u16* st = (lds_u16*)(uintptr_t)(t.lds + (uint32_t)slot * (C::kSlot * 2));
+    auto frags = [&](int ks, bf16x8 (&af)[C::NB], bf16x8 (&bm)[C::MB]) {
+#pragma unroll
+      for (int nb = 0; nb < C::NB; ++nb) {
+        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_i16x4*)(st + offA[nb] + ks * 16 * C::BN));
+        const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_i16x4*)(st + offA[nb] + ks * 16 * C::BN + 4 * C::BN));
+        const i16x8 w = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        af[nb] = __builtin_bit_cast(bf16x8, w);
+      }
+#pragma unroll
+      for (int mb = 0; mb < C::MB; ++mb)
+        bm[mb] = *(const __attribute__((address_space(3))) bf16x8*)(st + offB[ks] + mb * 32 * kBK);
+    };
+    auto mfmas = [&](const bf16x8 (&af)[C::NB], const bf16x8 (&bm)[C::MB]) {
+#pragma unroll
+      for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < C::MB; ++mb)
+          acc[nb][mb] =
+              __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[nb], bm[mb], acc[nb][mb], 0, 0, 0);
+    };
+    // the next step's fragments are read ahead of this step's MFMAs
+    bf16x8 af[2][C::NB], bm[2][C::MB];
+    frags(0, af[0], bm[0]);
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) {
+      if (ks + 1 < kKS) frags(ks + 1, af[(ks + 1) & 1], bm[(ks + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      mfmas(af[ks & 1], bm[ks & 1]);
+    }
+    slot = slot + 1 == C::S ? 0 : slot + 1;
+    fill = fill + 1 == C::S ? 0 : fill + 1;
+  }
+  waitcnt_vm<0>();   // no load may land in the ring under the epilogue
+  block_barrier();
+  small_store<C>(a, acc, smem, u, wave, lane, wn0, wm0, n0, cols_valid);
+}
+
 template <class C, class Args>
 __global__ void __launch_bounds__(C::kThr) small_gemm_kernel(Args a) {
   __shared__ __attribute__((aligned(1024))) uint16_t smem[C::S * C::kSlot];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int N = small_n(a);
-  const int NT = (N + C::BN - 1) / C::BN;
   RowShare<C::kThr> share;
   share.load(a);
   int rows_dev;
-  const SmallUnit u = small_unit<C::BM>(a.offsets, a.rows, a.E, NT, a.status, &rows_dev);
+  const SmallUnit u = small_unit<C::BM, C::BN>(a.offsets, a.rows, a.E,
+                                               (small_n(a) + C::BN - 1) / C::BN, a.status, &rows_dev);
   share.claim(a, rows_dev);
-  if (u.ok) {
-    const int n0 = u.nt * C::BN;
-    const int cols_valid = min(C::BN, N - n0);
-    SmallCtx<C> t;
-    t.lds = lds_addr(smem);
-    const int ldb = gemm_ldb(a);
-    t.rb = buffer_rsrc(gemm_b(a, u.e) + n0, ((long long)gemm_k(a) * ldb - n0) * 2);
-    t.ra = buffer_rsrc(gemm_a_base(a, u.r0), gemm_a_bytes(a, u.r0));
-#pragma unroll
-    for (int q = 0; q < C::WL; ++q) {
-      const int i = C::WL * wave + q;
-      const int flat = 64 * i + lane;   // 16-byte chunk of the stage
-      const int krow = flat / C::WC;
-      const int wc = (flat % C::WC) ^ C::wswz(krow);
-      t.wk[q] = krow;
-      t.wo[q] = 8 * wc < cols_valid ? 16u * (uint32_t)wc + 2u * (uint32_t)krow * (uint32_t)ldb
-                                    : kOutOfRange;
-    }
-#pragma unroll
-    for (int q = 0; q < C::XL; ++q) {
-      const int row = 8 * (C::XL * wave + q) + lane / 8;
-      const int lc = (lane % 8) ^ ((row / kXRowsPerLine) % kXChunks);
-      t.xk[q] = 8 * lc;
-      t.xo[q] = row < u.rows_valid ? small_a_off(a, u.r0, row) + 16u * (uint32_t)lc : kOutOfRange;
-    }
-    const int wn0 = (wave % C::WNW) * C::WN;
-    const int wm0 = (wave / C::WNW) * C::WM;
-    int offA[C::NB];
-    {
-      const int j = lane & 15;
-      const int krow = 8 * (lane >> 5) + (j >> 2);
-      const int uu = j & 3;
-      const int rg = (lane >> 4) & 1;
-#pragma unroll
-      for (int nb = 0; nb < C::NB; ++nb) {
-        const int col = wn0 + 32 * nb + 16 * rg + 8 * (uu & 1) + 4 * (uu >> 1);
-        offA[nb] = C::kXElems + krow * C::BN + (((col >> 3) ^ C::wswz(krow)) << 3) + (col & 7);
-      }
-    }
-    int offB[kKS];
-    {
-      const int m = wm0 + (lane & 31);
-#pragma unroll
-      for (int ks = 0; ks < kKS; ++ks) {
-        const int c = 2 * ks + (lane >> 5);
-        offB[ks] = m * kBK + ((c ^ ((m / kXRowsPerLine) % kXChunks)) << 3);
-      }
-    }
-    const int nk = (gemm_k(a) + kBK - 1) / kBK;
-#pragma unroll
-    for (int s = 0; s + 1 < C::S; ++s) small_issue<C>(a, t, s, s, wave);
-    f32x16 acc[C::NB][C::MB];
-#pragma unroll
-    for (int nb = 0; nb < C::NB; ++nb)
-#pragma unroll
-      for (int mb = 0; mb < C::MB; ++mb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[nb][mb][i] = 0.f;
-    int slot = 0, fill = C::S - 1;
-    for (int kt = 0; kt < nk; ++kt) {
-      waitcnt_vm<(C::S - 2) * C::LPS>();
-      block_barrier();
-      small_issue<C>(a, t, kt + C::S - 1, fill, wave);
-      lds_u16* st = (lds_u16*)(uintptr_t)(t.lds + (uint32_t)slot * (C::kSlot * 2));
-      auto frags = [&](int ks, bf16x8 (&af)[C::NB], bf16x8 (&bm)[C::MB]) {
-#pragma unroll
-        for (int nb = 0; nb < C::NB; ++nb) {
-          const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (lds_i16x4*)(st + offA[nb] + ks * 16 * C::BN));
-          const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (lds_i16x4*)(st + offA[nb] + ks * 16 * C::BN + 4 * C::BN));
-          const i16x8 w = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-          af[nb] = __builtin_bit_cast(bf16x8, w);
-        }
-#pragma unroll
-        for (int mb = 0; mb < C::MB; ++mb)
-          bm[mb] = *(const __attribute__((address_space(3))) bf16x8*)(st + offB[ks] + mb * 32 * kBK);
-      };
-      auto mfmas = [&](const bf16x8 (&af)[C::NB], const bf16x8 (&bm)[C::MB]) {
-#pragma unroll
-        for (int nb = 0; nb < C::NB; ++nb)
-#pragma unroll
-          for (int mb = 0; mb < C::MB; ++mb)
-            acc[nb][mb] =
-                __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[nb], bm[mb], acc[nb][mb], 0, 0, 0);
-      };
-      // the next step's fragments are read ahead of this step's MFMAs
-      bf16x8 af[2][C::NB], bm[2][C::MB];
-      frags(0, af[0], bm[0]);
-#pragma unroll
-      for (int ks = 0; ks < kKS; ++ks) {
-        if (ks + 1 < kKS) frags(ks + 1, af[(ks + 1) & 1], bm[(ks + 1) & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(af[ks & 1], bm[ks & 1]);
-      }
-      slot = slot + 1 == C::S ? 0 : slot + 1;
-      fill = fill + 1 == C::S ? 0 : fill + 1;
-    }
-    waitcnt_vm<0>();   // no load may land in the ring under the epilogue
-    block_barrier();
-    small_store<C>(a, acc, smem, u, wave, lane, wn0, wm0, n0, cols_valid);
-  }
+  if (u.ok) small_tile<C>(a, smem, u);
   share.finish(a);
+}
+
+// ---- medium and large batches: full 256 x 256 tiles, the rest in smaller ones --------
+// The first P workgroups (one per CU) run the tiles with 256 rows, chained as
+// in the persistent kernel; the workgroups after them run one smaller tile
+// each and start as the CUs become free, so that the hardware evens out the
+// partial last round and the padding is that of the small tiles:
+//  * 256 x 128 tiles over the right edge, where the last column block has at
+//    most 128 columns (2 I = 1408 is five blocks and a half);
+//  * 128 x 256 tiles over the rows past each expert's last full tile.
+constexpr int kEdge = kBN / 2;
+using MixedEdge = SmallTile<256, 128, 8, 2, 3>;
+using MixedBottom = SmallTile<128, 256, 8, 4, 3>;
+static_assert(sizeof(Smem) >= MixedEdge::S * MixedEdge::kSlot * 2 &&
+                  sizeof(Smem) >= MixedBottom::S * MixedBottom::kSlot * 2,
+              "the smaller tiles' rings overlay the whole of Smem");
+
+__host__ __device__ inline bool mixed_edge(int N) { return N % kBN != 0 && N % kBN <= kEdge; }
+
+// How a launch's rows and columns are cut: an expert has (count + pad) / 256
+// full m-tiles, the rows left are bottoms; `edge`: the last column block is
+// left to the edge tiles, else it is an ordinary (partly empty) block.
+struct MixedPlan {
+  int pad;
+  bool edge;
+  int blocks;                // column blocks of the full tiles and the bottoms
+  int full, edges, bottoms;  // full tiles, edge tiles, bottom m-units
+};
+
+__device__ __forceinline__ int mixed_bottoms(int count, int pad) {
+  return (max(0, count - (count + pad) / kBM * kBM) + MixedBottom::BM - 1) / MixedBottom::BM;
+}
+
+// x / n for 0 <= x < 2^24 and n > 0, by one reciprocal.
+__device__ __forceinline__ int small_div(int x, int n) {
+  int q = (int)((float)x * __builtin_amdgcn_rcpf((float)n));
+  q -= q * n > x;
+  q += (q + 1) * n <= x;
+  return q;
+}
+
+// The time of `full` tiles of fc each on P workgroups followed by `small`
+// tiles of hc each wherever a CU is free.
+__device__ __forceinline__ int mixed_time(int full, int small, int P, int fc, int hc) {
+  const int rounds = small_div(full, P), rem = full - rounds * P;
+  int t = rem > 0 ? fc : 0;
+  if (small > 0) {
+    const int behind = small_div(fc - 1, hc) + 1;   // small tiles a full one takes the place of
+    // `early` small tiles on each CU without a last full one: small / P at least
+    for (int early = small_div(small, P);; ++early) {
+      const int late = max(0, early - behind);
+      if ((P - rem) * early + rem * late >= small) {
+        t = max(t, early * hc);
+        break;
+      }
+      const int t_late = fc + (late + 1) * hc;
+      if (t_late < (early + 1) * hc && (P - rem) * early + rem * (late + 1) >= small) {
+        t = max(t, t_late);
+        break;
+      }
+    }
+  }
+  return rounds * fc + t;
+}
+
+// The plan with the least time, from the expert counts alone, so every wave
+// of the launch finds the same one.  Tile times for nk 64-deep stages, in
+// 10 ns (measured, 704 and 2048 deep: a full tile 1.5 us a stage + 4 us, a
+// smaller one 0.93 us a stage + 5.5 us, as it starts on its own).
+// (A launch of P workgroups alone takes full tiles for everything.)
+template <class Args>
+__device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
+  const int lane = threadIdx.x & 63;
+  const int N = small_n(a), nk = min(1024, (gemm_k(a) + kBK - 1) / kBK);
+  int all = 0, low = 0, mid = 0;   // m-tiles; experts with 1..128, 129..192 rows past them
+  for (int e0 = 0; e0 < a.E; e0 += 64) {
+    int cnt = 0;
+    if (e0 + lane < a.E) {
+      long long s = a.offsets[e0 + lane], en = a.offsets[e0 + lane + 1];
+      s = s < 0 ? 0 : (s > a.rows ? a.rows : s);
+      en = en < s ? s : (en > a.rows ? a.rows : en);
+      cnt = (int)(en - s);
+    }
+    const int past = cnt % kBM;
+    low += __builtin_popcountll(__ballot(past >= 1 && past <= 128));
+    mid += __builtin_popcountll(__ballot(past >= 129 && past <= 192));
+    all += (cnt + kBM - 1) / kBM;
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) all += __shfl_xor(all, d);
+  const int fc = 150 * nk + 400, hc = 93 * nk + 550;
+  // lane l weighs plan l: up to 192, 128 or no rows (l % 3) past an expert's
+  // last full tile, with the edge tiles from l = 3 on
+  const int p = lane % 3;
+  const bool edge = lane >= 3;
+  const int blocks = edge ? N / kBN : (N + kBN - 1) / kBN;
+  const int full = (all - (p == 0 ? low + mid : p == 1 ? low : 0)) * blocks;
+  const int bottoms = p == 0 ? low + 2 * mid : p == 1 ? low : 0;
+  const int edges = edge ? all : 0;
+  float cost = 3e38f;
+  const bool smaller = (int)gridDim.x > P;
+  if (smaller ? lane < (mixed_edge(N) ? 6 : 3) : lane == 2) {
+    const int small = edges + bottoms * blocks;
+    // the average load breaks ties (and counts for the power it takes); the
+    // smaller tiles have to save more than their own start
+    cost = (float)mixed_time(min(full, 1 << 22), min(small, 1 << 22), P, fc, hc) +
+           ((float)full * fc + (float)small * hc) * 0.25f / P + (small > 0 ? fc / 16 : 0);
+  }
+  int best = 2;
+  float least = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cost), 2));
+#pragma unroll
+  for (int l = 0; l < 6; ++l) {
+    const float c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cost), l));
+    if (c < least) {
+      least = c;
+      best = l;
+    }
+  }
+  MixedPlan plan;
+  plan.pad = best % 3 == 0 ? 63 : best % 3 == 1 ? 127 : kBM - 1;
+  plan.edge = best >= 3;
+  plan.blocks = __builtin_amdgcn_readlane(blocks, best);
+  plan.full = __builtin_amdgcn_readlane(full, best);
+  plan.edges = __builtin_amdgcn_readlane(edges, best);
+  plan.bottoms = __builtin_amdgcn_readlane(bottoms, best);
+  return plan;
+}
+
+// Unit j of the smaller tiles: edges first, then bottoms; each in eight equal
+// XCD shares, by each wave for itself.
+template <class Args>
+__device__ __forceinline__ SmallUnit mixed_unit(const Args& a, const MixedPlan& plan, int j,
+                                                bool* is_edge) {
+  const int lane = threadIdx.x & 63;
+  SmallUnit u = {0, 0, 0, 0, false};
+  const long long edge_chunk = ((long long)plan.edges + 7) >> 3;
+  *is_edge = j < 8 * edge_chunk;
+  const int per = *is_edge ? 1 : plan.blocks;   // column blocks per m-unit
+  const long long units = *is_edge ? plan.edges : (long long)plan.bottoms * per;
+  const long long chunk = (units + 7) >> 3;
+  const int i = *is_edge ? j : (int)(j - 8 * edge_chunk);
+  const long long unit = (long long)(i & 7) * chunk + (i >> 3);
+  u.ok = (i >> 3) < chunk && unit < units;
+  if (!u.ok) return u;
+  const int mt = (int)(unit / per);
+  int s = 0, cnt = 0, n = 0, v = 0, carry = 0, e0 = 0;
+  for (;; e0 += 64) {   // the chunk of 64 experts that holds m-unit mt
+    const int e = e0 + lane;
+    s = cnt = 0;
+    if (e < a.E) {
+      long long b = a.offsets[e], en = a.offsets[e + 1];
+      b = b < 0 ? 0 : (b > a.rows ? a.rows : b);
+      en = en < b ? b : (en > a.rows ? a.rows : en);
+      s = (int)b;
+      cnt = (int)(en - b);
+    }
+    n = *is_edge ? (cnt + kBM - 1) / kBM : mixed_bottoms(cnt, plan.pad);
+    v = n;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int x = __shfl_up(v, d);
+      if (lane >= d) v += x;
+    }
+    const int sum = __builtin_amdgcn_readlane(v, 63);
+    if (mt < carry + sum) break;
+    carry += sum;
+  }
+  const int l = (int)__builtin_ctzll(__ballot(carry + v > mt));
+  u.e = e0 + l;
+  const int first = carry + __builtin_amdgcn_readlane(v - n, l);
+  const int n_m = __builtin_amdgcn_readlane(n, l);
+  const int within = (int)(unit - (long long)first * per);
+  const int nt = within / n_m, mi = within - nt * n_m;
+  const int count = __builtin_amdgcn_readlane(cnt, l);
+  const int row = *is_edge ? mi * kBM : (count + plan.pad) / kBM * kBM + mi * MixedBottom::BM;
+  u.r0 = __builtin_amdgcn_readlane(s, l) + row;
+  u.rows_valid = min(*is_edge ? kBM : MixedBottom::BM, count - row);
+  u.n0 = *is_edge ? plan.blocks * kBN : nt * kBN;
+  return u;
+}
+
+__device__ __forceinline__ void mixed_prologue(Smem& sm, const KArgs& a) {
+  if (threadIdx.x == 0) {
+    sm.epoch = launch_epoch(a);   // load_experts synchronises
+    if (blockIdx.x == 0)
+      __hip_atomic_store(a.map_epoch, sm.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+__device__ __forceinline__ void mixed_prologue(Smem&, const G1Args&) {}
+__device__ __forceinline__ void mixed_inverse_map(const Smem& sm, const KArgs& a) {
+  consumer_prologue(sm, a, (long long)sm.start[a.E - 1] + sm.count[a.E - 1], false, a.P);
+  waitcnt_vm<0>();   // nothing the compiler tracks stays in flight in the tile loop
+}
+__device__ __forceinline__ void mixed_inverse_map(const Smem&, const G1Args&) {}
+
+template <class Args>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+mixed_gemm_kernel(Args a) {
+  __shared__ __attribute__((aligned(1024))) Smem sm;
+  const int P = a.P;
+  const MixedPlan plan = mixed_plan(a, P);
+  if ((int)blockIdx.x >= P) {
+    bool is_edge;
+    const SmallUnit u = mixed_unit(a, plan, (int)blockIdx.x - P, &is_edge);
+    if (!u.ok) return;
+    uint16_t* ring = reinterpret_cast<uint16_t*>(&sm);
+    if (is_edge)
+      small_tile<MixedEdge>(a, ring, u);
+    else
+      small_tile<MixedBottom>(a, ring, u);
+    return;
+  }
+  mixed_prologue(sm, a);
+  load_experts(sm, a, plan.pad);
+  a.ntps = plan.blocks;   // for decode_tile
+  const int total = sm.tile_prefix[a.E] * a.ntps;
+  const int full = total / P * P;   // whole rounds; the rest one each, spread over the XCDs
+  auto tile_of = [&](int k) {
+    if (k * P < full) return k * P + compute_index((int)blockIdx.x, 0, P);
+    if (k * P == full && (int)blockIdx.x < total - full)
+      return full + compute_index((int)blockIdx.x, 0, total - full);
+    return -1;
+  };
+  const int nk = (gemm_k(a) + kBK - 1) / kBK;
+  TileInfo cur = {0, 0, 0, 0, 0, 0};
+  TileCtx tctx;
+  bool filled = false;
+  int g = tile_of(0);
+  if (g >= 0) {
+    cur = decode_tile(sm, a, total, g);
+    if constexpr (!RowGather<Args>::on) {   // its loads fly during the inverse map's atomics
+      const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      tctx = make_ctx(sm, a, cur, wave);
+      issue_prologue(a, tctx, nk, 0, wave);
+      filled = true;
+    }
+  }
+  mixed_inverse_map(sm, a);
+  int base = 0;
+  for (int k = 0; g >= 0; ++k) {
+    const int g_next = tile_of(k + 1);
+    const bool next = g_next >= 0;
+    const TileInfo nt = next ? decode_tile(sm, a, total, g_next) : cur;
+    u64 t_mid[2];
+    compute_tile(sm, a, cur, filled, next, nt, base, t_mid, tctx);
+    base = (base + nk) % kStages;
+    filled = next;
+    cur = nt;
+    g = g_next;
+  }
 }
 
 // out[t, :] for every token: one wave per token and 256 columns.  The
@@ -412,19 +666,39 @@ __global__ void __launch_bounds__(C::kThr) small_gemm_kernel(Args a) {
 // inverse map under launch epoch *map_epoch; storing that as the workspace's
 // completed epoch ends the launch pair (only the first launch reads it).
 constexpr int kSmallCombineWaves = 4;
-__global__ void __launch_bounds__(kSmallCombineWaves * 64) small_combine_kernel(KArgs a) {
+
+// Rows j0 .. j0+U-1 of a token (its sorted rows in lanes of rs, gates in gs)
+// at CB column blocks: all loads first, then the sums in ascending order.
+template <int U, int CB, bool kNtLoad>
+__device__ __forceinline__ void small_gather(const uint16_t* y, int ypitch, int j0, int rs, int gs,
+                                             const int (&col)[CB], float (&acc)[CB][4]) {
+  u32x2 v[U][CB];
+#pragma unroll
+  for (int q = 0; q < U; ++q) {
+    const uint16_t* yr = y + (size_t)__builtin_amdgcn_readlane(rs, j0 + q) * ypitch;
+#pragma unroll
+    for (int b = 0; b < CB; ++b) {
+      const u32x2* p = (const u32x2*)(yr + col[b]);
+      v[q][b] = kNtLoad ? __builtin_nontemporal_load(p) : *p;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < U; ++q) {
+    const float g = __int_as_float(__builtin_amdgcn_readlane(gs, j0 + q));
+#pragma unroll
+    for (int b = 0; b < CB; ++b) fma4(acc[b], g, v[q][b]);
+  }
+}
+
+template <int CB, bool kNtLoad>
+__device__ __forceinline__ void small_combine_unit(const KArgs& a, u64 epoch, long long unit,
+                                                   int cbs) {
   const int lane = threadIdx.x & 63;
-  const u64 epoch =
-      __hip_atomic_load(a.map_epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    __hip_atomic_store(a.epoch_word, (uint32_t)(epoch + 1) == 0 ? epoch + 1 : epoch,
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int cbs = (a.H + 255) / 256;
-  const long long unit = (long long)blockIdx.x * kSmallCombineWaves +
-                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int t = (int)(unit / cbs);
-  if (t >= a.T) return;
-  const int col = (int)(unit - (long long)t * cbs) * 256 + 4 * lane;
+  const int c0 = (int)(unit - (long long)t * cbs) * 256 * CB + 4 * lane;
+  int col[CB];
+#pragma unroll
+  for (int b = 0; b < CB; ++b) col[b] = c0 + 256 * b < a.H ? c0 + 256 * b : 0;
   const u64 cnt_epoch = (epoch & ((1ull << (64 - kCntBits)) - 1)) << kCntBits;
   const int K = a.topk;
   const uint32_t have = epoch_count(a.tok_cnt[t], cnt_epoch);
@@ -441,19 +715,35 @@ __global__ void __launch_bounds__(kSmallCombineWaves * 64) small_combine_kernel(
   }
   const int rs = __builtin_amdgcn_ds_permute(4 * rank, r);
   const int gs = __builtin_amdgcn_ds_permute(4 * rank, __float_as_int(g));
-  const bool ok = col < a.H;
-  const uint16_t* y = a.Y + (ok ? col : 0);
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int j0 = 0; j0 < n; j0 += 8) {
-    u32x2 v[8];
+  float acc[CB][4];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int j = j0 + q < n ? j0 + q : n - 1;
-      v[q] = *(const u32x2*)(y + (size_t)__builtin_amdgcn_readlane(rs, j) * a.ypitch);
-    }
+  for (int b = 0; b < CB; ++b)
 #pragma unroll
-    for (int q = 0; q < 8; ++q)
-      if (j0 + q < n) fma4(acc, __int_as_float(__builtin_amdgcn_readlane(gs, j0 + q)), v[q]);
-  }
-  if (ok) *(f32x4*)(a.out + (size_t)t * a.H + col) = f32x4{acc[0], acc[1], acc[2], acc[3]};
+    for (int i = 0; i < 4; ++i) acc[b][i] = 0.f;
+  int j = 0;
+  for (; j + 8 <= n; j += 8) small_gather<8, CB, kNtLoad>(a.Y, a.ypitch, j, rs, gs, col, acc);
+  if (n - j >= 6) small_gather<6, CB, kNtLoad>(a.Y, a.ypitch, j, rs, gs, col, acc), j += 6;
+  if (n - j >= 4) small_gather<4, CB, kNtLoad>(a.Y, a.ypitch, j, rs, gs, col, acc), j += 4;
+  if (n - j >= 2) small_gather<2, CB, kNtLoad>(a.Y, a.ypitch, j, rs, gs, col, acc), j += 2;
+  if (n - j >= 1) small_gather<1, CB, kNtLoad>(a.Y, a.ypitch, j, rs, gs, col, acc);
+#pragma unroll
+  for (int b = 0; b < CB; ++b)
+    if (c0 + 256 * b < a.H)
+      __builtin_nontemporal_store(f32x4{acc[b][0], acc[b][1], acc[b][2], acc[b][3]},
+                                  (f32x4*)(a.out + (size_t)t * a.H + c0 + 256 * b));
+}
+
+template <int CB, bool kNtLoad>
+__global__ void __launch_bounds__(kSmallCombineWaves * 64) small_combine_kernel(KArgs a) {
+  const u64 epoch =
+      __hip_atomic_load(a.map_epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    __hip_atomic_store(a.epoch_word, (uint32_t)(epoch + 1) == 0 ? epoch + 1 : epoch,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int cbs = (a.H + 256 * CB - 1) / (256 * CB);
+  const long long units = (long long)a.T * cbs;
+  for (long long unit = (long long)blockIdx.x * kSmallCombineWaves +
+                        __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+       unit < units; unit += (long long)gridDim.x * kSmallCombineWaves)
+    small_combine_unit<CB, kNtLoad>(a, epoch, unit, cbs);
 }

@@ -1,6 +1,7 @@
-"""The small-batch launches (two launches without waits, four tile shapes)
-against the CPU oracle, and bitwise against the persistent kernel, which an
-explicit consumer count always takes."""
+"""The launches without dedicated consumers (two launches without waits; small
+tiles, or full tiles with smaller ones for the rest) against the CPU oracle,
+and bitwise against the persistent kernel, which an explicit consumer count
+always takes."""
 import numpy as np
 import pytest
 
@@ -36,6 +37,15 @@ CASES = {
     # expert row counts at the edges of the 64- and 128-row tiles, empty experts
     "edges_64": lambda: _edge_counts([63, 0, 64, 65, 1, 0, 33], 130, 520, 136, 9),
     "edges_128": lambda: _edge_counts([127, 128, 0, 129, 255, 256, 257, 1], 300, 4104, 24, 10),
+    # more than two 256 x 256 tiles per CU: full tiles, and 256 x 128 edges and
+    # 128 x 256 bottoms as the plan of the launch has it; rows past a full
+    # tile at the plan's limits (64, 128 and 192 of them), empty experts
+    "full_and_rest": lambda: _edge_counts([300] * 14, 400, 8320, 264, 21),
+    "full_edges": lambda: _edge_counts([256, 257, 0, 255, 192, 193, 320, 321, 384, 385, 448, 449,
+                                        64, 63, 1], 500, 8328, 40, 22),
+    "full_100_experts": lambda: _edge_counts([20 + (37 * e) % 310 for e in range(100)], 600, 1096,
+                                             72, 23),
+    "full_rounds": lambda: _edge_counts([2000, 2060, 1, 1990, 2048], 2100, 4104, 24, 24),
     "topk_64": lambda: custom(T=70, H=256, I=32, E=64, topk=64, L=1, seed=11),
 }
 
@@ -45,7 +55,7 @@ def _bits(a):
 
 
 @pytest.mark.parametrize("name", list(CASES))
-def test_small_batch_matches_oracle_and_persistent_kernel(gpu_lib, name):
+def test_stage_matches_oracle_and_persistent_kernel(gpu_lib, name):
     import gpu_util
     w = CASES[name]()
     print(f"{name}: T={w.T} H={w.H} I={w.I} E={w.E} k={w.topk} rows={w.Mtot}", flush=True)
@@ -100,11 +110,15 @@ UP = {
     "many_tiles": (64, 264, 672, 128, 4),
     "wide": (8, 128, 2048, 515, 2),
     "experts_200": (200, 256, 80, 60, 3),
+    # full tiles with smaller ones for the rest, with and without an edge
+    "full_edge": (14, 264, 2112, 1400, 3),
+    "full_no_edge": (10, 136, 1984, 2100, 4),
+    "full_100_experts": (100, 64, 1072, 3000, 6),
 }
 
 
 @pytest.mark.parametrize("name", list(UP))
-def test_small_batch_up_projection(gpu_lib, name):
+def test_up_projection_tiles(gpu_lib, name):
     """Against fp32 torch on the device: one bf16 rounding of the activation
     (2^-9 of its value) on top of fp32 sums of H products."""
     import torch
