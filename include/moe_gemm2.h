@@ -19,8 +19,8 @@
  * selector below evaluates its wave-quantized makespan model (Method,
  * "Wave-Quantized Pipeline Model" and Algorithm 1) to choose it.
  *
- * Calls that ask for no dedicated consumers (num_consumers 0 or -1, modes 0
- * and 2, no trace) run instead as two launches without flags or waits: a
+ * Calls that ask for no dedicated consumers (num_consumers 0 or -1, no
+ * trace; the atomic scatter while rows <= T topk) run instead as two launches without flags or waits: a
  * grouped GEMM whose tile sizes follow the batch, then the combine.  Both
  * ways compute every output element by the same operations in the same
  * order, so their results are bitwise equal.
@@ -395,7 +395,9 @@ int moe_gemm2_combine_traced(const void* x_perm, const void* w2, const int32_t* 
  *           additions varies from run to run, so the result does too, by
  *           rounding only.  Rows with an out-of-range token id are skipped
  *           and flagged; the topk bound per token is not checked (every
- *           in-range row is added);
+ *           in-range row is added).  With num_consumers 0 or -1, no trace and
+ *           rows <= T topk the same additions run as the second of the two
+ *           launches, one wave per token, without atomics;
  *   mode 2  owner-write over token bands: the wl->splits = L pipeline
  *           splits cut the routed rows instead of the columns.  Expert
  *           e's n_e = ceil(M_e/256) m-tiles are cut into L runs, band b

@@ -112,7 +112,9 @@ struct KArgs {
   int comm_tm_last;           // owner-write (column splits): tokens of the last split's
   int tasks_last;             //   tasks (finer, so that the launch ends evenly) and their count
   u64* epoch_word;            // the workspace's last completed launch epoch
-  u64* map_epoch;             // small batches: the epoch the first launch built the inverse map with
+  u64* map_epoch;             // two launches: the epoch the first built the inverse map with
+  u64* over_cnt;              // two launches in mode 1: launch-tagged count of the rows past topk
+                              // of their token, listed behind the inverse map (overflow_row)
   uint32_t* done_ctr;         // workgroups of this launch that have finished
   uint32_t* start_ctr;        // workgroups of this launch that have started
   int y_keep;                 // Y stores without the non-temporal bit
@@ -438,6 +440,21 @@ __device__ void load_experts(Smem& sm, const Args& a, int pad = kBM - 1) {
   __syncthreads();
 }
 
+// A row past its token's topk.  The owner-write modes drop and flag it; mode 1
+// adds every row, so there it goes to a list (of less than T topk rows: that
+// path runs only with rows <= T topk) after the inverse map's T topk slots.
+__device__ __forceinline__ void overflow_row(const KArgs& a, int r, u64 cnt_epoch) {
+  if (a.mode != 1) {
+    __hip_atomic_fetch_or(a.status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  __hip_atomic_fetch_max(a.over_cnt, cnt_epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const u64 old = __hip_atomic_fetch_add(a.over_cnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const long long slots = (long long)a.T * a.topk;
+  const long long i = (long long)(old & kCntMask);
+  if (i < slots) a.inv[slots + i] = r;
+}
+
 // What the consumers need before their first task, built by every
 // workgroup for its share: for the owner-write combine, the rows of each
 // token (the inverse map); for the atomic scatter, a zeroed output.  With
@@ -446,9 +463,9 @@ __device__ void load_experts(Smem& sm, const Args& a, int pad = kBM - 1) {
 // split's tiles (one L2 write-back for both).
 // The share is one of `shares` equal ones, by workgroup id.
 __device__ void consumer_prologue(const Smem& sm, const KArgs& a, long long rows_dev, bool publish,
-                                  int shares) {
+                                  int shares, bool zero_out) {
   const long long stride = (long long)shares * kThreads;
-  if (a.mode == 1) {
+  if (zero_out) {
     // out as 16-byte words, split into one contiguous range per workgroup
     const long long words = (long long)a.T * a.H / 4;
     const long long per = (words + shares - 1) / shares;
@@ -475,7 +492,7 @@ __device__ void consumer_prologue(const Smem& sm, const KArgs& a, long long rows
     const uint32_t slot =
         (old & ~kCntMask) == cnt_epoch ? (uint32_t)(old & kCntMask) : 0xffffffffu;
     if (slot >= (uint32_t)a.topk) {
-      __hip_atomic_fetch_or(a.status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      overflow_row(a, (int)r, cnt_epoch);
       continue;
     }
     a.inv[(long long)t * a.topk + slot] = (int32_t)r;
@@ -1733,7 +1750,7 @@ __device__ __forceinline__ void fused_body(Smem& sm, const KArgs& a) {
     issue_prologue(a, tctx, nk, 0, wave);
     filled = true;
   }
-  consumer_prologue(sm, a, rows_dev, !defer_inverse, (int)gridDim.x);
+  consumer_prologue(sm, a, rows_dev, !defer_inverse, (int)gridDim.x, a.mode == 1);
 
   if (b >= a.C) {   // compute role
     if (total > a.max_tiles) {  // cannot happen with sanitized offsets; stay in bounds
@@ -1956,7 +1973,8 @@ bool make_layout(const moe_workload_t* wl, Layout* L) {
   L->status = off;   // word 0: status bits; bytes 4..255: reserved;
                      // 256..319: per-split consumer task counters;
                      // 320: launch epoch (u64); 328: finished workgroups;
-                     // 332: started workgroups; 336: small batches' map epoch (u64)
+                     // 332: started workgroups; 336: the two launches' map epoch
+                     // (u64) and 344: mode 1's overflow count (u64)
   off += 512;
   L->wg_flags = off;
   off += (size_t)kMaxGrid * 4;
@@ -2504,6 +2522,7 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
   }
   a.epoch_word = reinterpret_cast<u64*>(ws + L.status + 320);
   a.map_epoch = reinterpret_cast<u64*>(ws + L.status + 336);
+  a.over_cnt = reinterpret_cast<u64*>(ws + L.status + 344);
   a.done_ctr = reinterpret_cast<uint32_t*>(ws + L.status + 328);
   a.start_ctr = reinterpret_cast<uint32_t*>(ws + L.status + 332);
   a.y_keep = 0;
@@ -2533,7 +2552,10 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
   if (clear && zero_async(workspace, L.Y, s) != hipSuccess) return MOE_ERR_HIP;
   // With no dedicated consumers asked for, two launches without waits (the
   // debugging aids act on the persistent kernel's waits, so they keep it).
-  if (!trace && num_consumers <= 0 && mode != 1 && !wait_env) {
+  // (Mode 1: the same additions without atomics, while its overflow list holds
+  // every row; 16.8 M fp32 atomics at T = 2048, H = 1024, top-8 take ~70 us.)
+  if (!trace && num_consumers <= 0 && !wait_env &&
+      (mode != 1 || (L.rows <= (long long)wl->T * wl->topk && L.rows < (long long)kCntMask))) {
     a.nsplit = wl->H;
     a.ysplit = round_up_line(wl->H);   // one segment; fits the column-split layout
     a.ypitch = a.ysplit + kYPad;

@@ -263,7 +263,7 @@ struct RowShare {
     const uint32_t slot =
         (old & ~kCntMask) == cnt_epoch ? (uint32_t)(old & kCntMask) : 0xffffffffu;
     if (slot >= (uint32_t)a.topk)
-      __hip_atomic_fetch_or(a.status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      overflow_row(a, r, cnt_epoch);
     else
       a.inv[(long long)t * a.topk + slot] = (int32_t)r;
   }
@@ -596,7 +596,7 @@ __device__ __forceinline__ void mixed_prologue(Smem& sm, const KArgs& a) {
 }
 __device__ __forceinline__ void mixed_prologue(Smem&, const G1Args&) {}
 __device__ __forceinline__ void mixed_inverse_map(const Smem& sm, const KArgs& a) {
-  consumer_prologue(sm, a, (long long)sm.start[a.E - 1] + sm.count[a.E - 1], false, a.P);
+  consumer_prologue(sm, a, (long long)sm.start[a.E - 1] + sm.count[a.E - 1], false, a.P, false);
   waitcnt_vm<0>();   // nothing the compiler tracks stays in flight in the tile loop
 }
 __device__ __forceinline__ void mixed_inverse_map(const Smem&, const G1Args&) {}
@@ -726,6 +726,19 @@ __device__ __forceinline__ void small_combine_unit(const KArgs& a, u64 epoch, lo
   if (n - j >= 4) small_gather<4, CB, kNtLoad>(a.Y, a.ypitch, j, rs, gs, col, acc), j += 4;
   if (n - j >= 2) small_gather<2, CB, kNtLoad>(a.Y, a.ypitch, j, rs, gs, col, acc), j += 2;
   if (n - j >= 1) small_gather<1, CB, kNtLoad>(a.Y, a.ypitch, j, rs, gs, col, acc);
+  if (a.mode == 1 && __builtin_amdgcn_readfirstlane(have) > (uint32_t)K) {
+    // a token with more than topk rows: the others are somewhere in the list
+    const long long slots = (long long)a.T * K;
+    const u64 listed = epoch_count(*a.over_cnt, cnt_epoch);
+    const int m = (int)(listed < (u64)slots ? listed : (u64)slots);
+    for (int i0 = 0; i0 < m; i0 += 64) {
+      const int row = i0 + lane < m ? a.inv[slots + i0 + lane] : -1;
+      u64 mine = __ballot(row >= 0 && a.token_ids[row < 0 ? 0 : row] == t);
+      const int gate = row >= 0 ? __float_as_int(a.gate_w[row]) : 0;
+      for (; mine; mine &= mine - 1)
+        small_gather<1, CB, kNtLoad>(a.Y, a.ypitch, (int)__builtin_ctzll(mine), row, gate, col, acc);
+    }
+  }
 #pragma unroll
   for (int b = 0; b < CB; ++b)
     if (c0 + 256 * b < a.H)

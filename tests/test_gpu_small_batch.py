@@ -100,6 +100,25 @@ def test_small_batch_unsorted_rows_and_no_rows(gpu_lib):
     assert (out == 0).all()
 
 
+@pytest.mark.parametrize("T,H,E", [(60, 520, 6), (2500, 4104, 5)], ids=["small", "full"])
+def test_scatter_adds_rows_past_topk(gpu_lib, T, H, E):
+    """Mode 1 without dedicated consumers adds every in-range row, also those
+    past a token's topk, and flags nothing; two such tokens, several times on
+    one workspace."""
+    import gpu_util
+    w = custom(T=T, H=H, I=40, E=E, topk=2, L=1, seed=14)
+    w.token_ids = w.token_ids.copy()
+    w.token_ids[::3] = 7          # one token owns a third of all rows
+    w.token_ids[1::31] = T - 1
+    ref = oc.combine_reference(w.x_perm, w.w2, w.expert_offsets, w.token_ids, w.gate_w, w.T)
+    dev = gpu_util.to_device(w)
+    ws = None
+    for C in (0, -1, 3, 0):
+        got, _, ws = gpu_util.run(w, C=C, dev=dev, workspace=ws, mode=1)
+        assert oc.rel_l2(got, ref) <= oc.REL_L2_TOL, C
+        assert oc.max_abs_ratio(got, ref) <= oc.MAX_ABS_TOL, C
+
+
 # the up-projection: E, H, I, T, topk for each tile shape, edges of its rows
 # and columns (2I = 96, 160, 1344 packed columns), a gather of repeated tokens
 UP = {
