@@ -2307,16 +2307,22 @@ hipError_t launch_small_tile(const Args& a, hipStream_t s) {
   hipLaunchKernelGGL((small_gemm_kernel<C, Args>), dim3((unsigned)grid), dim3(C::kThr), 0, s, a);
   return hipGetLastError();
 }
-using SmallTile128 = SmallTile<128, 128, 8, 4, 2>;   // 64 KB of LDS, two per CU
+using SmallTileWide = SmallTile<128, 256, 8, 4, 3, 32>;   // 72 KB of LDS, two per CU
+using SmallTile128 = SmallTile<128, 128, 8, 4, 2>;   // 64 KB, two per CU
 using SmallTile64 = SmallTile<64, 128, 8, 4, 2>;     // 48 KB, three per CU
 using SmallTile64Deep = SmallTile<64, 128, 8, 4, 3>; // 72 KB, two per CU
 using SmallTileNarrow = SmallTile<64, 64, 4, 2, 4>;  // 64 KB, two per CU
 
 // The tile: 128 rows where the experts hold more than 64 rows on average and
-// such tiles still give every CU one; else 64 rows, with the deeper ring
+// such tiles still give every CU one, 256 columns wide (a third less operand
+// traffic) if that holds for them too and no column block would be half
+// empty; else 64 rows, with the deeper ring
 // while there are too few for three per CU; and 64 x 64 where not even those
-// fill the CUs.  Measured (us): H = 2048, I = 704, E = 32, top-6, T = 512 (96
-// rows per expert) 26.5 with 128 rows, 29.0 with 64; T = 256 (48) 23.4 / 22.3;
+// fill the CUs.  Measured (us, inputs changing from call to call where two
+// widths are compared): H = 2048, I = 704, E = 32, top-6, T = 2048 78.4 with
+// 128 x 128, 70.1 with 128 x 256, T = 1024 45.0 / 40.1, T = 512 (96 rows per
+// expert) 30.7 / 28.7, its up-projection (2 I = 1408) of T = 1024 67.5 / 71.0;
+// T = 512 26.5 with 128 rows, 29.0 with 64; T = 256 (48) 23.4 / 22.3;
 // H = 1024, I = 512, E = 32, top-8, T = 64 (312 tiles) 13.4 with the shallow
 // ring, 12.4 with the deep one, and T = 256, 2048 columns (624 and more)
 // 22.3 / 23.4; the up-projection of H = 1352, I = 336, E = 11, T = 256 (132
@@ -2324,8 +2330,11 @@ using SmallTileNarrow = SmallTile<64, 64, 4, 2, 4>;  // 64 KB, two per CU
 template <class Args>
 hipError_t launch_small_gemm(const Args& a, int cus, hipStream_t s) {
   const long long n = a.E < a.rows ? a.E : a.rows;
-  if (a.rows > 64 * n && small_units<SmallTile128>(a) >= cus)
-    return launch_small_tile<SmallTile128>(a, s);
+  if (a.rows > 64 * n) {
+    if (!mixed_edge(a.nsplit) && small_units<SmallTileWide>(a) >= cus)
+      return launch_small_tile<SmallTileWide>(a, s);
+    if (small_units<SmallTile128>(a) >= cus) return launch_small_tile<SmallTile128>(a, s);
+  }
   const long long units = small_units<SmallTile64>(a);
   if (units < cus) return launch_small_tile<SmallTileNarrow>(a, s);
   return units < 2 * cus ? launch_small_tile<SmallTile64Deep>(a, s)
@@ -2350,21 +2359,27 @@ hipError_t launch_mixed_gemm(Args a, const DevInfo& d, hipStream_t s) {
   return hipGetLastError();
 }
 
-// tile x tile tiles of an average routing (half a tile's rows of padding per
-// expert), over N columns.
-long long expected_tiles(long long rows, int E, int N, int tile = kBN) {
+// Row tiles of an average routing (half a tile of padding per expert), times
+// 2 tile.
+long long expected_rows(long long rows, int E, int tile) {
   const long long n = E < rows ? E : rows;
-  return (2 * rows + tile * n) * ((N + tile - 1) / tile) / (2 * tile);
+  return 2 * rows + tile * n;
+}
+// 256 x 256 tiles of an average routing over N columns.
+long long expected_tiles(long long rows, int E, int N) {
+  return expected_rows(rows, E, kBM) * ((N + kBN - 1) / kBN) / (2 * kBM);
 }
 
 // The stage's grouped GEMM runs as small tiles up to two 256 x 256 tiles per
-// CU, beyond that as full tiles with smaller ones for the rest.  Measured
-// (us for the stage, small / full): 2.0 tiles per CU (H = 2048, I = 704, E =
-// 32, T = 2048) 68.8 / 70.3, 2.1 (H = 1024, I = 256, T = 4096) 49.2 / 49.0,
-// 2.5 (H = 2048, I = 704, E = 30, top-4, T = 4096) 85.0 / 78.5, 1.1 (H =
-// 1024, I = 512, E = 8, T = 8192) 43.5 / 46.8, 2.1 (T = 16384) 82.6 / 72.8.
-bool small_stage(long long rows, int E, int H, int cus) {
-  return expected_tiles(rows, E, H) <= 2LL * cus;
+// CU (three for reductions of 640 and more), beyond that as full tiles with
+// smaller ones for the rest.  Measured (us for the stage, small / full,
+// inputs changing from call to call): I = 704, H = 2048: 2.4 tiles per CU (E
+// = 30, top-4, T = 4096) 87.2 / 93.1, 2.75 (E = 32, top-6, T = 3072) 90.5 /
+// 97.3, 3.5 (T = 4096) 120.6 / 116.8; I = 512, H = 1024: 1.1 (E = 8, top-2,
+// T = 8192) 45.5 / 49, 2.1 (T = 16384) 84.3 / 82.0, 2.25 (E = 32, top-8, T =
+// 4096) 73.3 / 70.5.
+bool small_stage(long long rows, int E, int H, int I, int cus) {
+  return expected_tiles(rows, E, H) <= (I >= 640 ? 3LL : 2LL) * cus;
 }
 
 // Y this small stays in the 256 MB Infinity Cache until the combine reads it
@@ -2399,13 +2414,16 @@ hipError_t launch_combine(const KArgs& a, int cus, hipStream_t s) {
 // them, then 64 + 80 per 256 x 256 tile's work and CU.  Fitted to (us, small
 // / full): H = 2048, I = 704, E = 32, T = 512 33.5 / 53, 1024 60 / 55, 2048
 // 89 / 90, 4096 156 / 148, 8192 312 / 260; H = 1024, I = 512, E = 32, T =
-// 2048 50.6 / 54.1, 4096 88.8 / 87.6; H = 1352, I = 336, E = 11, T = 2048
-// 26.4 / 38.9, 4096 49.6 / 39.6.
+// 2048 50.2 / 54.1, 4096 85.8 / 88.7; H = 1352, I = 336, E = 11, T = 2048
+// 26.4 / 38.9, 4096 40.2 / 42.1, 8192 66.5 / 81.
 bool small_up_projection(long long rows, int E, int N, int cus) {
-  const long long units = expected_tiles(rows, E, N, 128);
+  // columns computed: whole blocks of 256, but 128 where an edge has its tiles
+  const int width = mixed_edge(N) ? kEdge : kBN;
+  const long long cols = (N + width - 1) / width * width;
+  const long long units = expected_rows(rows, E, 128) * (cols / 128) / 256;
   const long long small = units <= 2LL * cus ? 50LL * cus : 28LL * cus + 25 * units;
   const long long full = expected_tiles(rows, E, N) <= cus
-                             ? 82LL * cus : 64LL * cus + 80 * (rows * N / (kBM * kBN));
+                             ? 82LL * cus : 64LL * cus + 80 * (rows * cols / (kBM * kBN));
   return small < full;
 }
 
@@ -2560,7 +2578,7 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
     a.ysplit = round_up_line(wl->H);   // one segment; fits the column-split layout
     a.ypitch = a.ysplit + kYPad;
     a.y_keep = L.rows * (long long)a.ypitch * 2 <= kYKeepBytes;
-    hipError_t e = small_stage(L.rows, wl->E, wl->H, d.cus) ? launch_small_gemm(a, d.cus, s)
+    hipError_t e = small_stage(L.rows, wl->E, wl->H, wl->I, d.cus) ? launch_small_gemm(a, d.cus, s)
                                                            : launch_mixed_gemm(a, d, s);
     if (e == hipSuccess) e = launch_combine(a, d.cus, s);
     if (e == hipSuccess) return C;

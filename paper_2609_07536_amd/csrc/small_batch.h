@@ -26,18 +26,25 @@
 #pragma once
 
 // A tile of BM rows x BN columns, its NW waves WNW along the columns, a ring
-// of S 64-deep stages in LDS (S - 1 of them in flight).
+// of S stages of BK reduction steps in LDS (S - 1 of them in flight).  (32
+// steps, half lines of x, let two 128 x 256 tiles of eight waves share a CU:
+// four waves per SIMD and three quarters of the operand traffic of 128 x 128
+// tiles.  Sixteen waves on a 256 x 256 tile, or four on a 128 x 256 one,
+// measured slower: 123.9 and 155 against 118.9 us at T = 4096.)
 
-template <int BM_, int BN_, int NW_, int WNW_, int S_>
+template <int BM_, int BN_, int NW_, int WNW_, int S_, int BK_ = kBK>
 struct SmallTile {
+  static constexpr int BK = BK_, KS = BK / 16, XC = BK / 8;   // x chunks per row
+  static constexpr int kXPerLine = 256 / (2 * BK);
   static constexpr int BM = BM_, BN = BN_, NW = NW_, WNW = WNW_, S = S_;
   static constexpr int WMW = NW / WNW;
   static constexpr int WN = BN / WNW, WM = BM / WMW;   // a wave's columns and rows
   static constexpr int NB = WN / 32, MB = WM / 32;
   static constexpr int kThr = NW * 64;
-  static constexpr int XL = BM / 8 / NW, WL = BN / 8 / NW;   // 1 KB loads per wave and stage
+  static constexpr int XL = BM * BK / 512 / NW;   // 1 KB loads per wave and stage
+  static constexpr int WL = BN * BK / 512 / NW;
   static constexpr int LPS = XL + WL;
-  static constexpr int kXElems = BM * kBK, kWElems = BN * kBK;
+  static constexpr int kXElems = BM * BK, kWElems = BN * BK;
   static constexpr int kSlot = kXElems + kWElems;
   static constexpr int WC = BN / 8;       // 16-byte chunks per W row
   static_assert(BN >= 64 && BN <= 512 && XL >= 1 && WL >= 1, "loads per wave");
@@ -62,7 +69,7 @@ struct SmallCtx {
 template <class C, class Args>
 __device__ __forceinline__ void small_issue(const Args& a, const SmallCtx<C>& t, int kt, int slot,
                                             int wave) {
-  const int k0 = kt * kBK;
+  const int k0 = kt * C::BK;
   const uint32_t base = t.lds + (uint32_t)slot * (C::kSlot * 2);
 #pragma unroll
   for (int q = 0; q < C::WL; ++q) {
@@ -312,8 +319,8 @@ __device__ __forceinline__ void small_tile(const Args& a, uint16_t* smem, const 
   }
 #pragma unroll
   for (int q = 0; q < C::XL; ++q) {
-    const int row = 8 * (C::XL * wave + q) + lane / 8;
-    const int lc = (lane % 8) ^ ((row / kXRowsPerLine) % kXChunks);
+    const int row = 64 / C::XC * (C::XL * wave + q) + lane / C::XC;
+    const int lc = (lane % C::XC) ^ ((row / C::kXPerLine) % C::XC);
     t.xk[q] = 8 * lc;
     t.xo[q] = row < u.rows_valid ? small_a_off(a, u.r0, row) + 16u * (uint32_t)lc : kOutOfRange;
   }
@@ -331,16 +338,16 @@ __device__ __forceinline__ void small_tile(const Args& a, uint16_t* smem, const 
       offA[nb] = C::kXElems + krow * C::BN + (((col >> 3) ^ C::wswz(krow)) << 3) + (col & 7);
     }
   }
-  int offB[kKS];
+  int offB[C::KS];
   {
     const int m = wm0 + (lane & 31);
 #pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) {
+    for (int ks = 0; ks < C::KS; ++ks) {
       const int c = 2 * ks + (lane >> 5);
-      offB[ks] = m * kBK + ((c ^ ((m / kXRowsPerLine) % kXChunks)) << 3);
+      offB[ks] = m * C::BK + ((c ^ ((m / C::kXPerLine) % C::XC)) << 3);
     }
   }
-  const int nk = (gemm_k(a) + kBK - 1) / kBK;
+  const int nk = (gemm_k(a) + C::BK - 1) / C::BK;
 #pragma unroll
   for (int s = 0; s + 1 < C::S; ++s) small_issue<C>(a, t, s, s, wave);
   f32x16 acc[C::NB][C::MB];
@@ -368,7 +375,7 @@ __device__ __forceinline__ void small_tile(const Args& a, uint16_t* smem, const 
       }
 #pragma unroll
       for (int mb = 0; mb < C::MB; ++mb)
-        bm[mb] = *(const __attribute__((address_space(3))) bf16x8*)(st + offB[ks] + mb * 32 * kBK);
+        bm[mb] = *(const __attribute__((address_space(3))) bf16x8*)(st + offB[ks] + mb * 32 * C::BK);
     };
     auto mfmas = [&](const bf16x8 (&af)[C::NB], const bf16x8 (&bm)[C::MB]) {
 #pragma unroll
@@ -382,8 +389,8 @@ __device__ __forceinline__ void small_tile(const Args& a, uint16_t* smem, const 
     bf16x8 af[2][C::NB], bm[2][C::MB];
     frags(0, af[0], bm[0]);
 #pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) {
-      if (ks + 1 < kKS) frags(ks + 1, af[(ks + 1) & 1], bm[(ks + 1) & 1]);
+    for (int ks = 0; ks < C::KS; ++ks) {
+      if (ks + 1 < C::KS) frags(ks + 1, af[(ks + 1) & 1], bm[(ks + 1) & 1]);
       __builtin_amdgcn_sched_barrier(0);
       mfmas(af[ks & 1], bm[ks & 1]);
     }
