@@ -149,7 +149,7 @@ struct G1Args {
 // its reduction length, the row length of its B operand, B of expert e, and
 // where the A rows of a tile live: the base its loads address, the bytes
 // readable from there, and the byte offset of the tile's row `row`.
-__device__ __forceinline__ int gemm_k(const KArgs& a) { return a.I; }
+__host__ __device__ __forceinline__ int gemm_k(const KArgs& a) { return a.I; }
 __device__ __forceinline__ int gemm_ldb(const KArgs& a) { return a.H; }
 __device__ __forceinline__ const uint16_t* gemm_b(const KArgs& a, int e) {
   return a.w2 + (size_t)e * a.I * a.H;
@@ -163,7 +163,7 @@ __device__ __forceinline__ long long gemm_a_bytes(const KArgs& a, long long r0) 
 __device__ __forceinline__ uint32_t gemm_a_off(const int* rowtok, const KArgs& a, int row) {
   return (uint32_t)row * (uint32_t)a.I * 2u;
 }
-__device__ __forceinline__ int gemm_k(const G1Args& a) { return a.H; }
+__host__ __device__ __forceinline__ int gemm_k(const G1Args& a) { return a.H; }
 __device__ __forceinline__ int gemm_ldb(const G1Args& a) { return 2 * a.I; }
 __device__ __forceinline__ const uint16_t* gemm_b(const G1Args& a, int e) {
   return a.w1 + (size_t)e * a.H * (2 * a.I);
@@ -2308,20 +2308,21 @@ hipError_t launch_small_tile(const Args& a, hipStream_t s) {
   return hipGetLastError();
 }
 using SmallTileWide = SmallTile<128, 256, 8, 4, 3, 32>;   // 72 KB of LDS, two per CU
-using SmallTile128 = SmallTile<128, 128, 8, 4, 2>;   // 64 KB, two per CU
 using SmallTile64 = SmallTile<64, 128, 8, 4, 2>;     // 48 KB, three per CU
 using SmallTile64Deep = SmallTile<64, 128, 8, 4, 3>; // 72 KB, two per CU
 using SmallTileNarrow = SmallTile<64, 64, 4, 2, 4>;  // 64 KB, two per CU
 
 // The tile: 128 rows where the experts hold more than 64 rows on average and
 // such tiles still give every CU one, 256 columns wide (a third less operand
-// traffic) if that holds for them too and no column block would be half
-// empty; else 64 rows, with the deeper ring
+// traffic) if that holds for them too, a tile per CU for every 1024 of the
+// reduction (a longer one lasts longer, and its start weighs less than idle
+// CUs); else 64 rows, with the deeper ring
 // while there are too few for three per CU; and 64 x 64 where not even those
 // fill the CUs.  Measured (us, inputs changing from call to call where two
 // widths are compared): H = 2048, I = 704, E = 32, top-6, T = 2048 78.4 with
 // 128 x 128, 70.1 with 128 x 256, T = 1024 45.0 / 40.1, T = 512 (96 rows per
-// expert) 30.7 / 28.7, its up-projection (2 I = 1408) of T = 1024 67.5 / 71.0;
+// expert) 30.7 / 28.7, its up-projection (2048 deep) of T = 1536 (618 wide
+// tiles) 99.8 / 89.1, E = 30, top-4, T = 512 (270) 31.2 / 36.1;
 // T = 512 26.5 with 128 rows, 29.0 with 64; T = 256 (48) 23.4 / 22.3;
 // H = 1024, I = 512, E = 32, top-8, T = 64 (312 tiles) 13.4 with the shallow
 // ring, 12.4 with the deep one, and T = 256, 2048 columns (624 and more)
@@ -2331,7 +2332,8 @@ template <class Args>
 hipError_t launch_small_gemm(const Args& a, int cus, hipStream_t s) {
   const long long n = a.E < a.rows ? a.E : a.rows;
   if (a.rows > 64 * n) {
-    if (!mixed_edge(a.nsplit) && small_units<SmallTileWide>(a) >= cus)
+    const long long deep = gemm_k(a) > 1024 ? gemm_k(a) : 1024;
+    if (small_units<SmallTileWide>(a) * 1024 >= cus * deep)
       return launch_small_tile<SmallTileWide>(a, s);
     if (small_units<SmallTile128>(a) >= cus) return launch_small_tile<SmallTile128>(a, s);
   }
@@ -2410,18 +2412,18 @@ hipError_t launch_combine(const KArgs& a, int cus, hipStream_t s) {
 
 // The up-projection in 80ths of the time one full tile takes: small tiles
 // 50 while two per CU hold all of them, then 28 + 25 per 128 x 128 tile and
-// CU; full tiles with smaller ones for the rest 82 while one per CU holds
+// CU (23 where the full tiles leave an edge); full tiles with smaller ones for the rest 82 while one per CU holds
 // them, then 64 + 80 per 256 x 256 tile's work and CU.  Fitted to (us, small
 // / full): H = 2048, I = 704, E = 32, T = 512 33.5 / 53, 1024 60 / 55, 2048
 // 89 / 90, 4096 156 / 148, 8192 312 / 260; H = 1024, I = 512, E = 32, T =
-// 2048 50.2 / 54.1, 4096 85.8 / 88.7; H = 1352, I = 336, E = 11, T = 2048
+// 2048 50.2 / 54.1, 4096 85.8 / 88.7; E = 32, T = 3072 118 / 127.5; H = 1352, I = 336, E = 11, T = 2048
 // 26.4 / 38.9, 4096 40.2 / 42.1, 8192 66.5 / 81.
 bool small_up_projection(long long rows, int E, int N, int cus) {
   // columns computed: whole blocks of 256, but 128 where an edge has its tiles
   const int width = mixed_edge(N) ? kEdge : kBN;
   const long long cols = (N + width - 1) / width * width;
   const long long units = expected_rows(rows, E, 128) * (cols / 128) / 256;
-  const long long small = units <= 2LL * cus ? 50LL * cus : 28LL * cus + 25 * units;
+  const long long small = units <= 2LL * cus ? 50LL * cus : 28LL * cus + (width == kEdge ? 23 : 25) * units;
   const long long full = expected_tiles(rows, E, N) <= cus
                              ? 82LL * cus : 64LL * cus + 80 * (rows * cols / (kBM * kBN));
   return small < full;

@@ -402,6 +402,12 @@ __device__ __forceinline__ void small_tile(const Args& a, uint16_t* smem, const 
   small_store<C>(a, acc, smem, u, wave, lane, wn0, wm0, n0, cols_valid);
 }
 
+// Where the last column block has at most 128 columns, tiles 256 wide leave
+// it to 128 x 128 ones (mixed_edge), with as many threads and no more LDS.
+using SmallTile128 = SmallTile<128, 128, 8, 4, 2>;   // 64 KB of LDS, two per CU
+constexpr int kEdge = kBN / 2;
+__host__ __device__ inline bool mixed_edge(int N) { return N % kBN != 0 && N % kBN <= kEdge; }
+
 template <class C, class Args>
 __global__ void __launch_bounds__(C::kThr) small_gemm_kernel(Args a) {
   __shared__ __attribute__((aligned(1024))) uint16_t smem[C::S * C::kSlot];
@@ -411,7 +417,19 @@ __global__ void __launch_bounds__(C::kThr) small_gemm_kernel(Args a) {
   const SmallUnit u = small_unit<C::BM, C::BN>(a.offsets, a.rows, a.E,
                                                (small_n(a) + C::BN - 1) / C::BN, a.status, &rows_dev);
   share.claim(a, rows_dev);
-  if (u.ok) small_tile<C>(a, smem, u);
+  if (u.ok) {
+    if constexpr (C::BN == kBN) {
+      static_assert(C::BM == SmallTile128::BM && C::kThr == SmallTile128::kThr &&
+                        C::S * C::kSlot >= SmallTile128::S * SmallTile128::kSlot,
+                    "the edge tile in the wide tile's place");
+      if (mixed_edge(small_n(a)) && u.n0 + kEdge >= small_n(a))
+        small_tile<SmallTile128>(a, smem, u);
+      else
+        small_tile<C>(a, smem, u);
+    } else {
+      small_tile<C>(a, smem, u);
+    }
+  }
   share.finish(a);
 }
 
@@ -423,14 +441,11 @@ __global__ void __launch_bounds__(C::kThr) small_gemm_kernel(Args a) {
 //  * 256 x 128 tiles over the right edge, where the last column block has at
 //    most 128 columns (2 I = 1408 is five blocks and a half);
 //  * 128 x 256 tiles over the rows past each expert's last full tile.
-constexpr int kEdge = kBN / 2;
 using MixedEdge = SmallTile<256, 128, 8, 2, 3>;
 using MixedBottom = SmallTile<128, 256, 8, 4, 3>;
 static_assert(sizeof(Smem) >= MixedEdge::S * MixedEdge::kSlot * 2 &&
                   sizeof(Smem) >= MixedBottom::S * MixedBottom::kSlot * 2,
               "the smaller tiles' rings overlay the whole of Smem");
-
-__host__ __device__ inline bool mixed_edge(int N) { return N % kBN != 0 && N % kBN <= kEdge; }
 
 // How a launch's rows and columns are cut: an expert has (count + pad) / 256
 // full m-tiles, the rows left are bottoms; `edge`: the last column block is

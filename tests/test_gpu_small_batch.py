@@ -30,8 +30,8 @@ CASES = {
     "deep_ring": lambda: custom(T=64, H=1024, I=72, E=32, topk=8, L=1, seed=5),
     "many_tiles": lambda: custom(T=128, H=2056, I=104, E=64, topk=4, L=1,
                                  routing=("zipf", 1.0), seed=6),
-    # 128 x 256 tiles (32-deep stages, a reduction that ends inside one) and
-    # 128 x 128 ones (the last column block at most half full)
+    # 128 x 256 tiles (32-deep stages, a reduction that ends inside one), and
+    # with 128 x 128 ones for a last column block that is at most half full
     "wide": lambda: custom(T=515, H=8192, I=72, E=8, topk=2, L=2, seed=7),
     "wide_edges": lambda: _edge_counts([127, 128, 129, 255, 256, 257, 70], 300, 8456, 40, 24),
     "half_block": lambda: custom(T=515, H=4168, I=64, E=8, topk=2, L=1, seed=25),
@@ -131,7 +131,7 @@ UP = {
     "deep_ring": (32, 520, 512, 64, 8),
     "many_tiles": (64, 264, 672, 128, 4),
     "wide": (8, 136, 4096, 515, 2),
-    "half_block": (8, 128, 2096, 515, 2),
+    "half_block": (8, 128, 4160, 515, 2),
     "experts_200": (200, 256, 80, 60, 3),
     # full tiles with smaller ones for the rest, with and without an edge
     "full_edge": (14, 264, 2112, 1400, 3),
