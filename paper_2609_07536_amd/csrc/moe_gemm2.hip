@@ -25,6 +25,9 @@
 // counter), else they leave the tasks to the workgroups started later, so a
 // launch that shares the GPU with another never waits on workgroups that
 // cannot get a CU.  Every consumer wait is bounded.
+//
+// Calls without dedicated consumers (and without a trace) run as two launches
+// without waits instead: small_batch.h, which also holds the up-projection.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -2329,12 +2332,15 @@ using SmallTileNarrow = SmallTile<64, 64, 4, 2, 4>;  // 64 KB, two per CU
 // 22.3 / 23.4; the up-projection of H = 1352, I = 336, E = 11, T = 256 (132
 // 64 x 128 tiles) 11.5 with them, 9.8 with 64 x 64.
 template <class Args>
+bool wide_tiles(const Args& a, int cus) {
+  const long long deep = gemm_k(a) > 1024 ? gemm_k(a) : 1024;
+  return small_units<SmallTileWide>(a) * 1024 >= cus * deep;
+}
+template <class Args>
 hipError_t launch_small_gemm(const Args& a, int cus, hipStream_t s) {
   const long long n = a.E < a.rows ? a.E : a.rows;
   if (a.rows > 64 * n) {
-    const long long deep = gemm_k(a) > 1024 ? gemm_k(a) : 1024;
-    if (small_units<SmallTileWide>(a) * 1024 >= cus * deep)
-      return launch_small_tile<SmallTileWide>(a, s);
+    if (wide_tiles(a, cus)) return launch_small_tile<SmallTileWide>(a, s);
     if (small_units<SmallTile128>(a) >= cus) return launch_small_tile<SmallTile128>(a, s);
   }
   const long long units = small_units<SmallTile64>(a);
@@ -2412,20 +2418,25 @@ hipError_t launch_combine(const KArgs& a, int cus, hipStream_t s) {
 
 // The up-projection in 80ths of the time one full tile takes: small tiles
 // 50 while two per CU hold all of them, then 28 + 25 per 128 x 128 tile and
-// CU (23 where the full tiles leave an edge); full tiles with smaller ones for the rest 82 while one per CU holds
-// them, then 64 + 80 per 256 x 256 tile's work and CU.  Fitted to (us, small
-// / full): H = 2048, I = 704, E = 32, T = 512 33.5 / 53, 1024 60 / 55, 2048
-// 89 / 90, 4096 156 / 148, 8192 312 / 260; H = 1024, I = 512, E = 32, T =
-// 2048 50.2 / 54.1, 4096 85.8 / 88.7; E = 32, T = 3072 118 / 127.5; H = 1352, I = 336, E = 11, T = 2048
-// 26.4 / 38.9, 4096 40.2 / 42.1, 8192 66.5 / 81.
-bool small_up_projection(long long rows, int E, int N, int cus) {
+// CU (23 where the full tiles leave an edge), but two rounds of 128 x 128
+// ones at least 90; full tiles with smaller ones for the rest 82 while one
+// per CU holds them, then 64 + 80 per 256 x 256 tile's work and CU.  Fitted to
+// (us, small / full): H = 2048, I = 704, E = 32, T = 512 33.5 / 53, 700 68 /
+// 61 (inputs changing from call to call), 1024 60 / 55, 2048 89 / 90, 3072
+// 118 / 127.5, 4096 156 / 148, 8192 312 / 260; H = 1024, I = 512, E = 32, T =
+// 800 29.9 / 31.8, 2048 50.2 / 54.1, 4096 85.8 / 88.7; H = 1352, I = 336, E =
+// 11, T = 2048 26.4 / 38.9, 3600 45.0 / 42.8, 8192 66.5 / 81.
+bool small_up_projection(const G1Args& a, int cus) {
+  const int N = a.nsplit;
   // columns computed: whole blocks of 256, but 128 where an edge has its tiles
   const int width = mixed_edge(N) ? kEdge : kBN;
   const long long cols = (N + width - 1) / width * width;
-  const long long units = expected_rows(rows, E, 128) * (cols / 128) / 256;
-  const long long small = units <= 2LL * cus ? 50LL * cus : 28LL * cus + (width == kEdge ? 23 : 25) * units;
-  const long long full = expected_tiles(rows, E, N) <= cus
-                             ? 82LL * cus : 64LL * cus + 80 * (rows * cols / (kBM * kBN));
+  const long long units = expected_rows(a.rows, a.E, 128) * (cols / 128) / 256;
+  long long small = units <= 2LL * cus ? 50LL * cus
+                                       : 28LL * cus + (width == kEdge ? 23 : 25) * units;
+  if (units > 2LL * cus && small < 90LL * cus && !wide_tiles(a, cus)) small = 90LL * cus;
+  const long long full = expected_tiles(a.rows, a.E, N) <= cus
+                             ? 82LL * cus : 64LL * cus + 80 * (a.rows * cols / (kBM * kBN));
   return small < full;
 }
 
@@ -2573,7 +2584,8 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
   // With no dedicated consumers asked for, two launches without waits (the
   // debugging aids act on the persistent kernel's waits, so they keep it).
   // (Mode 1: the same additions without atomics, while its overflow list holds
-  // every row; 16.8 M fp32 atomics at T = 2048, H = 1024, top-8 take ~70 us.)
+  // every row; its 16.8 M fp32 atomics at T = 2048, H = 1024, top-8 took about
+  // 70 us of 107, the two launches take 30.)
   if (!trace && num_consumers <= 0 && !wait_env &&
       (mode != 1 || (L.rows <= (long long)wl->T * wl->topk && L.rows < (long long)kCntMask))) {
     a.nsplit = wl->H;
@@ -2788,7 +2800,7 @@ int launch_gemm1(const void* hidden, const void* w1, const int32_t* expert_offse
   a.E = wl->E;
   a.nsplit = 2 * wl->I;
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  const hipError_t e = small_up_projection(rows, wl->E, a.nsplit, d.cus)
+  const hipError_t e = small_up_projection(a, d.cus)
                            ? launch_small_gemm(a, d.cus, s)
                            : launch_mixed_gemm(a, d, s);
   return e == hipSuccess ? MOE_OK : MOE_ERR_HIP;

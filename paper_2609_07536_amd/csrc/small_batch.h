@@ -1,17 +1,18 @@
-// The stage and the up-projection for small and medium batches (included by
-// moe_gemm2.hip, inside its anonymous namespace, after its helpers).
+// The up-projection, and the stage without dedicated consumers (included by
+// moe_gemm2.hip, inside its anonymous namespace, after its helpers): a grouped
+// GEMM with tiles that follow the batch, then a launch that combines, one wave
+// per token and 256 or 512 columns.  The kernel boundary is the only
+// dependency: no flags, no waits, nothing that has to be resident.  (The two
+// launches run back to back on the GPU: no gap in a kernel trace.)
 //
 // What bounds such a launch: below about 64 rows per expert the weights (W2
 // of 32 experts at H = 2048, I = 704 is 92 MB, 18.6 us at the rate a large
-// copy reaches here), above it the tiles' operand loads.  The persistent
-// kernel's 256 x 256 tiles give a workgroup 16-20 us of work whatever the
-// rows in them, and its publish, readiness and acquire another 10-15 us.
-// Here one launch runs the grouped GEMM with small tiles, one workgroup per
-// tile and two or three workgroups per CU, so that one's loads cover
-// another's start, epilogue and waits; a second launch combines, one wave
-// per token and 256 columns.  The kernel boundary is the only dependency:
-// no flags, no waits, nothing resident.  (The two launches run back to back
-// on the GPU: no gap in a kernel trace.)
+// copy reaches here), above it the tiles' operand traffic and the matrix
+// cores.  The persistent kernel's 256 x 256 tiles give a workgroup 16-20 us of
+// work whatever the rows in them, and its publish, readiness and acquire
+// another 10-15 us.  Small tiles, one workgroup each and two or three per CU,
+// let one's loads cover another's start, epilogue and waits; large batches
+// run full tiles and give the small ones the rest (mixed_gemm_kernel).
 //
 // Every output element is the same chain as in the persistent kernel: the
 // same 32x32x16 MFMAs over the whole reduction in the same order, Y rounded
@@ -20,9 +21,13 @@
 //
 // Measured (us, GPU time, persistent kernel -> this path), H = 2048, I = 704,
 // E = 32, top-6, uniform routing: T = 1 36.7 -> 9.8, 8 40.7 -> 17.9,
-// 64 44.0 -> 21.3, 256 46.4 -> 22.3, 512 49.6 -> 26.5, 1024 55.9 -> 45,
-// 2048 80 -> 71, 4096 123 -> 118; its up-projection T = 1 44.3 -> 12.3,
-// 64 46.6 -> 28.4, 256 47.3 -> 29.7, 512 48.2 -> 33.5.
+// 64 44.0 -> 21.3, 256 46.4 -> 22.3, 512 49.6 -> 26.5, 1024 55.9 -> 40,
+// 2048 80 -> 61, 4096 124.9 -> 104, 8192 200 -> 187, 16384 359 -> 347,
+// 32768 777 -> 751; its up-projection T = 1 44.3 -> 12.3, 64 46.6 -> 28.4,
+// 256 47.3 -> 29.7, 512 48.2 -> 33.5, 2048 104 -> 90, 4096 160 -> 148,
+// 16384 526 -> 504.  The largest GEMMs are bound by the power the chip may
+// draw: the up-projection of T = 16384 takes 553 us with random operands and
+// 405 us with zeros, and 526 us whether or not its loads hit the L2.
 #pragma once
 
 // A tile of BM rows x BN columns, its NW waves WNW along the columns, a ring
@@ -433,7 +438,7 @@ __global__ void __launch_bounds__(C::kThr) small_gemm_kernel(Args a) {
   share.finish(a);
 }
 
-// ---- medium and large batches: full 256 x 256 tiles, the rest in smaller ones --------
+// ---- large batches: full 256 x 256 tiles, the rest in smaller ones -----------------
 // The first P workgroups (one per CU) run the tiles with 256 rows, chained as
 // in the persistent kernel; the workgroups after them run one smaller tile
 // each and start as the CUs become free, so that the hardware evens out the
@@ -441,6 +446,10 @@ __global__ void __launch_bounds__(C::kThr) small_gemm_kernel(Args a) {
 //  * 256 x 128 tiles over the right edge, where the last column block has at
 //    most 128 columns (2 I = 1408 is five blocks and a half);
 //  * 128 x 256 tiles over the rows past each expert's last full tile.
+// (H = 2048, I = 704, E = 32, up-projection, us, whole rounds of full tiles ->
+// this: T = 4096 2.6 rounds 160 -> 148, T = 8192 267 -> 260, T = 16384 526 ->
+// 504; the idle CUs it fills are worth less than their share of the time,
+// because the others then run at a higher clock.)
 using MixedEdge = SmallTile<256, 128, 8, 2, 3>;
 using MixedBottom = SmallTile<128, 256, 8, 4, 3>;
 static_assert(sizeof(Smem) >= MixedEdge::S * MixedEdge::kSlot * 2 &&
@@ -518,6 +527,10 @@ __device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
   }
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) all += __shfl_xor(all, d);
+  all = __builtin_amdgcn_readfirstlane(all);
+  // one round of full tiles holds everything (nothing to weigh: 3 us less)
+  const int whole = (N + kBN - 1) / kBN;
+  if (all <= small_div(P, whole)) return {kBM - 1, false, whole, all * whole, 0, 0};
   const int fc = 150 * nk + 400, hc = 93 * nk + 550;
   // lane l weighs plan l: up to 192, 128 or no rows (l % 3) past an expert's
   // last full tile, with the edge tiles from l = 3 on
@@ -532,9 +545,10 @@ __device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
   if (smaller ? lane < (mixed_edge(N) ? 6 : 3) : lane == 2) {
     const int small = edges + bottoms * blocks;
     // the average load breaks ties (and counts for the power it takes); the
-    // smaller tiles have to save more than their own start
+    // smaller tiles have to save a sixth of a full one (one round of full tiles
+    // for everything 35.6 us, with smaller ones on its idle CUs 39.7)
     cost = (float)mixed_time(min(full, 1 << 22), min(small, 1 << 22), P, fc, hc) +
-           ((float)full * fc + (float)small * hc) * 0.25f / P + (small > 0 ? fc / 16 : 0);
+           ((float)full * fc + (float)small * hc) * 0.25f / P + (small > 0 ? fc / 6 : 0);
   }
   int best = 2;
   float least = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cost), 2));
@@ -682,9 +696,11 @@ mixed_gemm_kernel(Args a) {
 
 // out[t, :] for every token: one wave per token and 256 columns.  The
 // token's count, its rows (in inverse-map order, sorted by rank across the
-// lanes) and then its gates and Y rows are two dependent round trips; with
-// many tokens it is bound by the Y rows read and the output written (T =
-// 1024, H = 2048, top-6: 34 MB in 8.0 us).  The first launch built the
+// lanes) and then its gates and Y rows are two dependent round trips (3.0 us
+// for one token); with many tokens it is bound by the Y rows read and the
+// output written (T = 16384, H = 2048, top-6: 537 MB in 85.5 us, 6.3 TB/s).
+// Only the rows a token has are read: padding its list to eight with repeated
+// rows cost 8% of the stage at top-4, T = 16384.  The first launch built the
 // inverse map under launch epoch *map_epoch; storing that as the workspace's
 // completed epoch ends the launch pair (only the first launch reads it).
 constexpr int kSmallCombineWaves = 4;
