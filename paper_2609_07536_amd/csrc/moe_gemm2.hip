@@ -2418,23 +2418,21 @@ hipError_t launch_combine(const KArgs& a, int cus, hipStream_t s) {
 
 // The up-projection in 80ths of the time one full tile takes: small tiles
 // 50 while two per CU hold all of them, then 28 + 25 per 128 x 128 tile and
-// CU (23 where the full tiles leave an edge), but two rounds of 128 x 128
-// ones at least 90; full tiles with smaller ones for the rest 82 while one
-// per CU holds them, then 64 + 80 per 256 x 256 tile's work and CU.  Fitted to
-// (us, small / full): H = 2048, I = 704, E = 32, T = 512 33.5 / 53, 700 68 /
-// 61 (inputs changing from call to call), 1024 60 / 55, 2048 89 / 90, 3072
-// 118 / 127.5, 4096 156 / 148, 8192 312 / 260; H = 1024, I = 512, E = 32, T =
+// CU (23 where the full tiles leave an edge); full tiles with smaller ones
+// for the rest 82 while one per CU holds them, then 64 + 80 per 256 x 256
+// tile's work and CU.  Fitted to (us, small / full): H = 2048, I = 704, E =
+// 32, T = 512 33.5 / 53, 1024 60 / 55, 2048 89 / 90, 3072 118 / 127.5, 4096
+// 156 / 148, 8192 312 / 260, E = 30, top-4, T = 1024 48.5 / 63.6; H = 1024, I = 512, E = 32, T =
 // 800 29.9 / 31.8, 2048 50.2 / 54.1, 4096 85.8 / 88.7; H = 1352, I = 336, E =
-// 11, T = 2048 26.4 / 38.9, 3600 45.0 / 42.8, 8192 66.5 / 81.
+// 11, T = 2048 26.4 / 38.9, 8192 66.5 / 81.
 bool small_up_projection(const G1Args& a, int cus) {
   const int N = a.nsplit;
   // columns computed: whole blocks of 256, but 128 where an edge has its tiles
   const int width = mixed_edge(N) ? kEdge : kBN;
   const long long cols = (N + width - 1) / width * width;
   const long long units = expected_rows(a.rows, a.E, 128) * (cols / 128) / 256;
-  long long small = units <= 2LL * cus ? 50LL * cus
-                                       : 28LL * cus + (width == kEdge ? 23 : 25) * units;
-  if (units > 2LL * cus && small < 90LL * cus && !wide_tiles(a, cus)) small = 90LL * cus;
+  const long long small = units <= 2LL * cus ? 50LL * cus
+                                             : 28LL * cus + (width == kEdge ? 23 : 25) * units;
   const long long full = expected_tiles(a.rows, a.E, N) <= cus
                              ? 82LL * cus : 64LL * cus + 80 * (a.rows * cols / (kBM * kBN));
   return small < full;
