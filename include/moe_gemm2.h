@@ -324,7 +324,9 @@ int moe_gemm2_workspace_init(void* workspace, size_t workspace_bytes, void* stre
  *   workspace       device memory of at least moe_gemm2_workspace_size(wl)
  *                   bytes, 256-byte aligned, zeroed once by
  *                   moe_gemm2_workspace_init; calls that may overlap in
- *                   time need distinct workspaces.  The workspace keeps a
+ *                   time need distinct workspaces (host threads may share
+ *                   one on one stream: nothing else is enqueued on it between
+ *                   the launches of a call).  The workspace keeps a
  *                   launch epoch that each launch advances on the device,
  *                   so a call captured in a HIP graph may be replayed
  *                   (with wl->host_expert_counts NULL the call reads

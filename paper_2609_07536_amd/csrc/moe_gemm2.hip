@@ -2186,6 +2186,17 @@ bool workspace_needs_clear(const void* ws, uint64_t sig) {
   return true;
 }
 
+// A call's launches on one workspace (the clear for a new layout, the GEMM that
+// builds the inverse map and Y, the combine that reads them) are enqueued
+// without another host thread's launches on that workspace in between: one of
+// a fixed set of locks, by the workspace's address, is held over them (two
+// workspaces that share one only enqueue one after the other).
+constexpr int kWsLocks = 64;
+std::mutex g_ws_launch[kWsLocks];
+std::mutex& workspace_launch_lock(const void* ws) {
+  return g_ws_launch[((uint64_t)(uintptr_t)ws >> 8) * 0x9e3779b97f4a7c15ull >> 58];
+}
+
 // The workspace of moe_gemm2_combine_noalloc, for callers that cannot
 // allocate device memory: one array in the code object's device memory,
 // which every GPU the library runs on holds (at its own address) until the
@@ -2570,6 +2581,7 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   const uint64_t sig = layout_signature(wl, L);
+  std::lock_guard<std::mutex> in_order(workspace_launch_lock(workspace));
   bool clear;
   if (layout_slot) {
     std::lock_guard<std::mutex> lk(g_ws_mu);

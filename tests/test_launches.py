@@ -1,0 +1,37 @@
+"""CPU: the kernels that calls launch and the order in which they do, through a
+stand-in HIP runtime that records launches (launch_recorder.py)."""
+import pytest
+
+import launch_recorder
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    return launch_recorder.start(tmp_path_factory.mktemp("recorder"))
+
+
+@pytest.mark.parametrize("op", ["combine", "noalloc"])
+def test_threads_sharing_a_workspace_do_not_split_a_call(recorder, op):
+    """Host threads that enqueue calls on one stream with one workspace (the
+    calls then never overlap in time): nothing another thread enqueues comes
+    between the launches of a call, which hand the inverse map and Y over
+    through the workspace, nor between the clear for a new layout and them."""
+    got = launch_recorder.run(recorder, f'''
+import threading
+recorder.recorder_pause_us(300)
+shapes = [dict(T=64, H=512, I=64, E=8, topk=2), dict(T=40, H=512, I=64, E=8, topk=2, C=3),
+          dict(T=90, H=256, I=64, E=4, topk=2, mode=1)]
+def work(i):
+    for n in range(6):
+        assert call("{op}", **shapes[(i + n) % 3]) >= 0
+threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+for t in threads: t.start()
+for t in threads: t.join()
+result = launches()
+''')
+    assert sum("small_combine" in k for k, *_ in got) == 16
+    for i, (kernel, _, _, thread) in enumerate(got):
+        if "small_combine" in kernel:
+            assert "gemm_kernel" in got[i - 1][0] and got[i - 1][3] == thread, got[i - 1:i + 1]
+        elif "fill_zero" in kernel:
+            assert "fill_zero" not in got[i + 1][0] and got[i + 1][3] == thread, got[i:i + 2]
