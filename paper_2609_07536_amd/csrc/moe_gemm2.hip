@@ -118,6 +118,8 @@ struct KArgs {
   u64* map_epoch;             // two launches: the epoch the first built the inverse map with
   u64* over_cnt;              // two launches in mode 1: launch-tagged count of the rows past topk
                               // of their token, listed behind the inverse map (overflow_row)
+  u64* unit_ctr;              // two launches: [8] launch-tagged count of the smaller tiles an
+                              // XCD's workgroups have taken
   uint32_t* done_ctr;         // workgroups of this launch that have finished
   uint32_t* start_ctr;        // workgroups of this launch that have started
   int y_keep;                 // Y stores without the non-temporal bit
@@ -1190,7 +1192,10 @@ __device__ void compute_tile(Smem& sm, const Args& a, const TileInfo& ti, bool f
   }
   static_assert(kLoadsPerOperand % kNB == 0 && kLoadsPerOperand / kNB <= kKS, "load spread");
   static_assert(kStages == 2, "the boundary loop refills one stage ahead");
-  // boundaries whose freed slot takes a stage of this tile
+  // boundaries whose freed slot takes a stage of this tile (the loop, 1016 bytes,
+  // from the start of an instruction cache line: the stage at T = 16384, H =
+  // 2048, I = 704, E = 32 379.3 us, from the middle of one 383.1)
+  asm volatile(".p2align 6");
   for (int kt = 0; kt + kStages < nk; ++kt) {
     wait_stage(kStages - 2);
     block_barrier();
@@ -1977,7 +1982,8 @@ bool make_layout(const moe_workload_t* wl, Layout* L) {
                      // 256..319: per-split consumer task counters;
                      // 320: launch epoch (u64); 328: finished workgroups;
                      // 332: started workgroups; 336: the two launches' map epoch
-                     // (u64) and 344: mode 1's overflow count (u64)
+                     // (u64), 344: mode 1's overflow count (u64) and 352..415:
+                     // the smaller tiles taken on each XCD (u64 each)
   off += 512;
   L->wg_flags = off;
   off += (size_t)kMaxGrid * 4;
@@ -2362,18 +2368,19 @@ hipError_t launch_small_gemm(const Args& a, int cus, hipStream_t s) {
 
 template <class Args>
 hipError_t launch_mixed_gemm(Args a, const DevInfo& d, hipStream_t s) {
-  const int N = a.nsplit;
   a.P = d.occ * d.cus;
-  const long long n = a.E < a.rows ? a.E : a.rows;
-  // the most smaller tiles of any plan: an edge per 256 rows or part of them,
-  // two bottoms (129 rows or more) or one per expert and column block, each
-  // kind rounded to eight
-  const long long edges = mixed_edge(N) ? (a.rows - n) / kBM + n : 0;
-  long long bottoms = n + a.rows / (MixedBottom::BM + 1);
-  if (bottoms > 2 * n) bottoms = 2 * n;
-  bottoms *= (N + kBN - 1) / kBN;
-  long long grid = a.P + (edges + 7) / 8 * 8 + (bottoms + 7) / 8 * 8;
-  if (grid > kMaxSmallGrid) grid = a.P;   // past what a launch can hold: full tiles only
+  int grid = a.P;
+  if constexpr (!RowGather<Args>::on) {
+    // the stage's workgroups for smaller tiles: no more than a plan can have (two
+    // bottoms, of 129 rows or more, or one per expert and column block; an
+    // edge per 256 rows or part of them), a multiple of eight
+    const long long n = a.E < a.rows ? a.E : a.rows;
+    long long units = n + a.rows / (MixedBottom::BM + 1);
+    if (units > 2 * n) units = 2 * n;
+    units *= (a.nsplit + kBN - 1) / kBN;
+    if (mixed_edge(a.nsplit)) units += (a.rows - n) / kBM + n;
+    grid += (int)((units < 2 * a.P ? units : 2 * a.P) + 7) / 8 * 8;
+  }
   hipLaunchKernelGGL((mixed_gemm_kernel<Args>), dim3((unsigned)grid), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
@@ -2563,6 +2570,7 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
   a.epoch_word = reinterpret_cast<u64*>(ws + L.status + 320);
   a.map_epoch = reinterpret_cast<u64*>(ws + L.status + 336);
   a.over_cnt = reinterpret_cast<u64*>(ws + L.status + 344);
+  a.unit_ctr = reinterpret_cast<u64*>(ws + L.status + 352);
   a.done_ctr = reinterpret_cast<uint32_t*>(ws + L.status + 328);
   a.start_ctr = reinterpret_cast<uint32_t*>(ws + L.status + 332);
   a.y_keep = 0;

@@ -300,9 +300,14 @@ struct RowShare {
   __device__ __forceinline__ void finish(const G1Args&) {}
 };
 
-// The unit's tile, by C::kThr threads with the ring at smem.
-template <class C, class Args>
-__device__ __forceinline__ void small_tile(const Args& a, uint16_t* smem, const SmallUnit& u) {
+// The unit's tile, by C::kThr threads with the ring at smem; `meanwhile` runs
+// while the ring fills.
+struct Nothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <class C, class Args, class Meanwhile = Nothing>
+__device__ __forceinline__ void small_tile(const Args& a, uint16_t* smem, const SmallUnit& u,
+                                           Meanwhile meanwhile = Meanwhile()) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n0 = u.n0, N = small_n(a);
@@ -355,6 +360,7 @@ __device__ __forceinline__ void small_tile(const Args& a, uint16_t* smem, const 
   const int nk = (gemm_k(a) + C::BK - 1) / C::BK;
 #pragma unroll
   for (int s = 0; s + 1 < C::S; ++s) small_issue<C>(a, t, s, s, wave);
+  meanwhile();
   f32x16 acc[C::NB][C::MB];
 #pragma unroll
   for (int nb = 0; nb < C::NB; ++nb)
@@ -439,22 +445,28 @@ __global__ void __launch_bounds__(C::kThr) small_gemm_kernel(Args a) {
 }
 
 // ---- large batches: full 256 x 256 tiles, the rest in smaller ones -----------------
-// The first P workgroups (one per CU) run the tiles with 256 rows, chained as
-// in the persistent kernel; the workgroups after them run one smaller tile
-// each and start as the CUs become free, so that the hardware evens out the
-// partial last round and the padding is that of the small tiles:
+// P workgroups (one per CU) run the tiles with 256 rows, chained as in the
+// persistent kernel, and after them the smaller tiles, which fill the partial
+// last round and keep the padding small:
 //  * 256 x 128 tiles over the right edge, where the last column block has at
 //    most 128 columns (2 I = 1408 is five blocks and a half);
 //  * 128 x 256 tiles over the rows past each expert's last full tile.
-// (H = 2048, I = 704, E = 32, up-projection, us, whole rounds of full tiles ->
-// this: T = 4096 2.6 rounds 160 -> 148, T = 8192 267 -> 260, T = 16384 526 ->
-// 504; the idle CUs it fills are worth less than their share of the time,
-// because the others then run at a higher clock.)
+// The stage starts further workgroups for those, 2 P at most, as the CUs become
+// free; each takes some by its index and then others from a counter per XCD in
+// the workspace.  The up-projection, whose workspace other calls may share,
+// gives each of its P workgroups as many, after its full tiles, as the plan says
+// for one with and one without a tile of the last round.  (With a workgroup
+// for every smaller tile that the host's bound allows, most found out for
+// themselves, on a CU of their own, that there was nothing for them: T =
+// 16384, H = 2048, I = 704, E = 32, up-projection 531.8 us, now 520.7, and E =
+// 1024, H = 512, I = 128, T = 16384 146 / 108.  In fixed shares the stage too
+// waits for a full tile's stores before the first smaller one: 388.4 us against
+// 383.3.)
 using MixedEdge = SmallTile<256, 128, 8, 2, 3>;
 using MixedBottom = SmallTile<128, 256, 8, 4, 3>;
-static_assert(sizeof(Smem) >= MixedEdge::S * MixedEdge::kSlot * 2 &&
-                  sizeof(Smem) >= MixedBottom::S * MixedBottom::kSlot * 2,
-              "the smaller tiles' rings overlay the whole of Smem");
+static_assert(offsetof(Smem, task) >= MixedEdge::S * MixedEdge::kSlot * 2 &&
+                  offsetof(Smem, task) >= MixedBottom::S * MixedBottom::kSlot * 2,
+              "the smaller tiles' rings lie over Smem, but not over what hands them out");
 
 // How a launch's rows and columns are cut: an expert has (count + pad) / 256
 // full m-tiles, the rows left are bottoms; `edge`: the last column block is
@@ -464,6 +476,7 @@ struct MixedPlan {
   bool edge;
   int blocks;                // column blocks of the full tiles and the bottoms
   int full, edges, bottoms;  // full tiles, edge tiles, bottom m-units
+  int early, late;           // smaller tiles of a workgroup without / with a last full tile
 };
 
 __device__ __forceinline__ int mixed_bottoms(int count, int pad) {
@@ -479,34 +492,36 @@ __device__ __forceinline__ int small_div(int x, int n) {
 }
 
 // The time of `full` tiles of fc each on P workgroups followed by `small`
-// tiles of hc each wherever a CU is free.
-__device__ __forceinline__ int mixed_time(int full, int small, int P, int fc, int hc) {
+// tiles of hc each, early on a workgroup without a last full tile and late on
+// one with it: as few as hold them all.
+__device__ __forceinline__ float mixed_time(int full, int small, int P, int fc, int hc, int& early,
+                                            int& late) {
   const int rounds = small_div(full, P), rem = full - rounds * P;
   int t = rem > 0 ? fc : 0;
+  early = late = 0;
   if (small > 0) {
     const int behind = small_div(fc - 1, hc) + 1;   // small tiles a full one takes the place of
-    // `early` small tiles on each CU without a last full one: small / P at least
-    for (int early = small_div(small, P);; ++early) {
-      const int late = max(0, early - behind);
+    for (early = small_div(small, P);; ++early) {   // small / P at least
+      late = max(0, early - behind);
       if ((P - rem) * early + rem * late >= small) {
         t = max(t, early * hc);
         break;
       }
       const int t_late = fc + (late + 1) * hc;
       if (t_late < (early + 1) * hc && (P - rem) * early + rem * (late + 1) >= small) {
+        ++late;
         t = max(t, t_late);
         break;
       }
     }
   }
-  return rounds * fc + t;
+  return (float)rounds * fc + t;
 }
 
 // The plan with the least time, from the expert counts alone, so every wave
 // of the launch finds the same one.  Tile times for nk 64-deep stages, in
 // 10 ns (measured, 704 and 2048 deep: a full tile 1.5 us a stage + 4 us, a
 // smaller one 0.93 us a stage + 5.5 us, as it starts on its own).
-// (A launch of P workgroups alone takes full tiles for everything.)
 template <class Args>
 __device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
   const int lane = threadIdx.x & 63;
@@ -530,7 +545,7 @@ __device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
   all = __builtin_amdgcn_readfirstlane(all);
   // one round of full tiles holds everything (nothing to weigh: 3 us less)
   const int whole = (N + kBN - 1) / kBN;
-  if (all <= small_div(P, whole)) return {kBM - 1, false, whole, all * whole, 0, 0};
+  if (all <= small_div(P, whole)) return {kBM - 1, false, whole, all * whole, 0, 0, 0, 0};
   const int fc = 150 * nk + 400, hc = 93 * nk + 550;
   // lane l weighs plan l: up to 192, 128 or no rows (l % 3) past an expert's
   // last full tile, with the edge tiles from l = 3 on
@@ -541,13 +556,15 @@ __device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
   const int bottoms = p == 0 ? low + 2 * mid : p == 1 ? low : 0;
   const int edges = edge ? all : 0;
   float cost = 3e38f;
-  const bool smaller = (int)gridDim.x > P;
-  if (smaller ? lane < (mixed_edge(N) ? 6 : 3) : lane == 2) {
-    const int small = edges + bottoms * blocks;
+  int early = 0, late = 0;
+  const long long small_all = edges + (long long)bottoms * blocks;
+  // (past 2^22 tiles, where small_div ends, only plan 2: full tiles alone)
+  if (lane < (mixed_edge(N) ? 6 : 3) && full < (1 << 22) && small_all < (1 << 22)) {
+    const int small = (int)small_all;
     // the average load breaks ties (and counts for the power it takes); the
     // smaller tiles have to save a sixth of a full one (one round of full tiles
     // for everything 35.6 us, with smaller ones on its idle CUs 39.7)
-    cost = (float)mixed_time(min(full, 1 << 22), min(small, 1 << 22), P, fc, hc) +
+    cost = mixed_time(full, small, P, fc, hc, early, late) +
            ((float)full * fc + (float)small * hc) * 0.25f / P + (small > 0 ? fc / 6 : 0);
   }
   int best = 2;
@@ -567,26 +584,93 @@ __device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
   plan.full = __builtin_amdgcn_readlane(full, best);
   plan.edges = __builtin_amdgcn_readlane(edges, best);
   plan.bottoms = __builtin_amdgcn_readlane(bottoms, best);
+  plan.early = __builtin_amdgcn_readlane(early, best);
+  plan.late = __builtin_amdgcn_readlane(late, best);
   return plan;
 }
 
-// Unit j of the smaller tiles: edges first, then bottoms; each in eight equal
-// XCD shares, by each wave for itself.
+// The smaller tiles that the up-projection's workgroup b of P takes, the first
+// full % P of which have a tile of the last round: first, first + step, ...
+// below end, `count` at most.  Each XCD (b mod 8) has a range of neighbouring
+// units, as long as its workgroups' share of the whole; those without a last
+// full tile take its front in turns, the others its back.
+struct MixedShare {
+  int first, step, count, end;
+  __device__ __forceinline__ int ahead() {
+    const int j = first;
+    first += step;
+    return count-- > 0 && j < end ? j : -1;
+  }
+  __device__ __forceinline__ int claim(Smem&, const G1Args&) const { return -1; }
+};
+__device__ __forceinline__ MixedShare mixed_share(const MixedPlan& plan, int b, int P) {
+  const int rem = plan.full % P;
+  const int units = plan.edges + plan.bottoms * plan.blocks;
+  auto on_xcd = [](int n, int x) { return (n + 7 - x) >> 3; };   // workgroups below n on XCD x
+  int before = 0, all = 0, mine = 0;   // how many the workgroups of XCDs hold
+  for (int x = 0; x < 8; ++x) {
+    const int with = on_xcd(rem, x), cap = (on_xcd(P, x) - with) * plan.early + with * plan.late;
+    if (x < (b & 7)) before += cap;
+    if (x == (b & 7)) mine = cap;
+    all += cap;
+  }
+  const int lo = (int)((long long)units * before / all);
+  const int with = on_xcd(rem, b & 7), without = on_xcd(P, b & 7) - with;
+  MixedShare sh;
+  sh.end = (int)((long long)units * (before + mine) / all);
+  if (b < rem)
+    sh.first = lo + without * plan.early + (b >> 3), sh.step = with, sh.count = plan.late;
+  else
+    sh.first = lo + (b >> 3) - with, sh.step = without, sh.count = plan.early;
+  return sh;
+}
+
+// The smaller tiles that the stage's i-th workgroup behind the first P takes:
+// of its XCD's (i mod 8) eighth of the units [lo, lo + units) those by its index,
+// known ahead, for all but the last two rounds of the `per` workgroups there
+// (one round at least), then what a launch-tagged counter gives.  (sm.task lies
+// past the rings.)
+struct MixedQueue {
+  int lo, units, per, given, j;
+  __device__ __forceinline__ MixedQueue(const KArgs& a, const MixedPlan& plan, int i) {
+    const int all = plan.edges + plan.bottoms * plan.blocks, chunk = (all + 7) >> 3;
+    lo = (i & 7) * chunk;
+    units = max(0, min(chunk, all - lo));
+    per = ((int)gridDim.x - a.P) >> 3;   // (a multiple of eight workgroups)
+    given = max(units / per - 2, 1) * per;
+    j = i >> 3;
+  }
+  __device__ __forceinline__ int ahead() {   // by index
+    const int k = j;
+    j += per;
+    return k < given && k < units ? lo + k : -1;
+  }
+  __device__ __forceinline__ int claim(Smem& sm, const KArgs& a) const {   // from the counter
+    if (given >= units) return -1;
+    if (threadIdx.x == 0) {
+      u64* ctr = a.unit_ctr + ((blockIdx.x - a.P) & 7);
+      const u64 tag = (launch_epoch(a) & ((1ull << (64 - kCntBits)) - 1)) << kCntBits;
+      __hip_atomic_fetch_max(ctr, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const u64 n = __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sm.task = (int)min(n & kCntMask, (u64)(units - given));
+    }
+    __syncthreads();
+    const int k = given + __builtin_amdgcn_readfirstlane(sm.task);
+    return k < units ? lo + k : -1;
+  }
+};
+
+// Unit `i` of the smaller tiles: edges first, then bottoms; by each wave for
+// itself.  (A negative i: none.)
 template <class Args>
-__device__ __forceinline__ SmallUnit mixed_unit(const Args& a, const MixedPlan& plan, int j,
-                                                bool* is_edge) {
+__device__ __forceinline__ SmallUnit mixed_unit(const Args& a, const MixedPlan& plan, int i) {
+  if (i < 0) return {0, 0, 0, 0, false};
   const int lane = threadIdx.x & 63;
-  SmallUnit u = {0, 0, 0, 0, false};
-  const long long edge_chunk = ((long long)plan.edges + 7) >> 3;
-  *is_edge = j < 8 * edge_chunk;
-  const int per = *is_edge ? 1 : plan.blocks;   // column blocks per m-unit
-  const long long units = *is_edge ? plan.edges : (long long)plan.bottoms * per;
-  const long long chunk = (units + 7) >> 3;
-  const int i = *is_edge ? j : (int)(j - 8 * edge_chunk);
-  const long long unit = (long long)(i & 7) * chunk + (i >> 3);
-  u.ok = (i >> 3) < chunk && unit < units;
-  if (!u.ok) return u;
-  const int mt = (int)(unit / per);
+  SmallUnit u = {0, 0, 0, 0, true};
+  const bool edge = i < plan.edges;
+  const int per = edge ? 1 : plan.blocks;   // column blocks per m-unit
+  const int unit = edge ? i : i - plan.edges;
+  const int mt = unit / per;
   int s = 0, cnt = 0, n = 0, v = 0, carry = 0, e0 = 0;
   for (;; e0 += 64) {   // the chunk of 64 experts that holds m-unit mt
     const int e = e0 + lane;
@@ -598,7 +682,7 @@ __device__ __forceinline__ SmallUnit mixed_unit(const Args& a, const MixedPlan& 
       s = (int)b;
       cnt = (int)(en - b);
     }
-    n = *is_edge ? (cnt + kBM - 1) / kBM : mixed_bottoms(cnt, plan.pad);
+    n = edge ? (cnt + kBM - 1) / kBM : mixed_bottoms(cnt, plan.pad);
     v = n;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -613,13 +697,13 @@ __device__ __forceinline__ SmallUnit mixed_unit(const Args& a, const MixedPlan& 
   u.e = e0 + l;
   const int first = carry + __builtin_amdgcn_readlane(v - n, l);
   const int n_m = __builtin_amdgcn_readlane(n, l);
-  const int within = (int)(unit - (long long)first * per);
+  const int within = unit - first * per;
   const int nt = within / n_m, mi = within - nt * n_m;
   const int count = __builtin_amdgcn_readlane(cnt, l);
-  const int row = *is_edge ? mi * kBM : (count + plan.pad) / kBM * kBM + mi * MixedBottom::BM;
+  const int row = edge ? mi * kBM : (count + plan.pad) / kBM * kBM + mi * MixedBottom::BM;
   u.r0 = __builtin_amdgcn_readlane(s, l) + row;
-  u.rows_valid = min(*is_edge ? kBM : MixedBottom::BM, count - row);
-  u.n0 = *is_edge ? plan.blocks * kBN : nt * kBN;
+  u.rows_valid = min(edge ? kBM : MixedBottom::BM, count - row);
+  u.n0 = edge ? plan.blocks * kBN : nt * kBN;
   return u;
 }
 
@@ -637,22 +721,63 @@ __device__ __forceinline__ void mixed_inverse_map(const Smem& sm, const KArgs& a
 }
 __device__ __forceinline__ void mixed_inverse_map(const Smem&, const G1Args&) {}
 
+// The smaller tiles of a workgroup, the ring over sm up to sm.task: those that
+// queue.ahead() gives, then those of queue.claim() (-1 at the end of each).  A
+// tile that is known ahead is looked up while the one before fills its ring:
+// after that one's epilogue the offsets' loads would wait for its stores.
+// (Every wave of the workgroup is past its use of sm on entry; the barrier keeps
+// a tile's loads behind the one before.)
+template <class Args, class Queue>
+__device__ __forceinline__ void mixed_small_tiles(Smem& sm, const Args& a, const MixedPlan& plan,
+                                                  Queue& queue) {
+  uint16_t* ring = reinterpret_cast<uint16_t*>(&sm);
+  int j = queue.ahead();
+  SmallUnit u = mixed_unit(a, plan, j);
+  while (u.ok) {
+    const bool edge = j < plan.edges;
+    SmallUnit u_next;
+    auto look_up = [&] {
+      j = queue.ahead();
+      u_next = mixed_unit(a, plan, j);
+    };
+    if (edge)
+      small_tile<MixedEdge>(a, ring, u, look_up);
+    else
+      small_tile<MixedBottom>(a, ring, u, look_up);
+    block_barrier();
+    if (!u_next.ok) {
+      j = queue.claim(sm, a);
+      u_next = mixed_unit(a, plan, j);
+    }
+    u = u_next;
+  }
+}
+
 template <class Args>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 mixed_gemm_kernel(Args a) {
+  constexpr bool kUp = RowGather<Args>::on;   // the up-projection
   __shared__ __attribute__((aligned(1024))) Smem sm;
   const int P = a.P;
+  if constexpr (!kUp) {
+    if ((int)blockIdx.x >= P) {
+      const MixedPlan plan = mixed_plan(a, P);
+      MixedQueue queue(a, plan, (int)blockIdx.x - P);
+      mixed_small_tiles(sm, a, plan, queue);
+      return;
+    }
+  }
   const MixedPlan plan = mixed_plan(a, P);
-  if ((int)blockIdx.x >= P) {
-    bool is_edge;
-    const SmallUnit u = mixed_unit(a, plan, (int)blockIdx.x - P, &is_edge);
-    if (!u.ok) return;
-    uint16_t* ring = reinterpret_cast<uint16_t*>(&sm);
-    if (is_edge)
-      small_tile<MixedEdge>(a, ring, u);
+  // (what the smaller tiles need later waits in LDS, in the token bands' room)
+  MixedPlan& kept_plan = *reinterpret_cast<MixedPlan*>(sm.band_pre);
+  MixedShare& kept_share = *reinterpret_cast<MixedShare*>(sm.band_pre + 16);
+  static_assert(sizeof(MixedPlan) <= 64 && sizeof(sm.band_pre) >= 64 + sizeof(MixedShare), "room");
+  if (kUp && threadIdx.x == 0) {   // load_experts synchronises
+    kept_plan = plan;
+    if (plan.early + plan.late > 0)
+      kept_share = mixed_share(plan, (int)blockIdx.x, P);
     else
-      small_tile<MixedBottom>(a, ring, u);
-    return;
+      kept_share = {0, 0, 0, 0};
   }
   mixed_prologue(sm, a);
   load_experts(sm, a, plan.pad);
@@ -672,7 +797,7 @@ mixed_gemm_kernel(Args a) {
   int g = tile_of(0);
   if (g >= 0) {
     cur = decode_tile(sm, a, total, g);
-    if constexpr (!RowGather<Args>::on) {   // its loads fly during the inverse map's atomics
+    if constexpr (!kUp) {   // its loads fly during the inverse map's atomics
       const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
       tctx = make_ctx(sm, a, cur, wave);
       issue_prologue(a, tctx, nk, 0, wave);
@@ -691,6 +816,13 @@ mixed_gemm_kernel(Args a) {
     filled = next;
     cur = nt;
     g = g_next;
+  }
+  if constexpr (kUp) {
+    const MixedPlan rest = kept_plan;
+    MixedShare share = kept_share;
+    waitcnt_vm<63>();   // (these reads; its own loads compute_tile has waited for)
+    block_barrier();
+    mixed_small_tiles(sm, a, rest, share);
   }
 }
 

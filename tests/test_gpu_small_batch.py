@@ -163,3 +163,62 @@ def test_up_projection_tiles(gpu_lib, name):
         ref[a:b] = torch.nn.functional.silu(h[:, :I]) * h[:, I:]
     # fp32 sums of up to 2048 products of unit variance: about 1e-6 each way
     assert (got.float() - ref).abs().le(2 ** -8 * ref.abs() + 2e-4).all()
+
+
+# E, H, I, rows of expert e: many more smaller tiles than CUs, so that a
+# workgroup takes several (by its index and from the counter; in fixed shares),
+# with and without a narrower last column block
+MANY = {
+    "bottoms": (300, 2048, 1040, lambda e: 30 + e % 31),
+    "edges": (700, 264, 512, lambda e: 1 + 5 * e % 90),
+    "both": (150, 1096, 1040, lambda e: 100 + 7 * e % 400),
+    "few_full": (270, 2304, 768, lambda e: 240 + e % 40 if e % 3 else 0),
+}
+
+
+@pytest.mark.parametrize("name", list(MANY))
+def test_several_smaller_tiles_per_workgroup(gpu_lib, name):
+    """The stage bitwise against the persistent kernel (three consumers), the
+    up-projection against fp32 torch, three calls each on one workspace."""
+    import torch
+
+    from paper_2609_07536_amd import binding as B
+    E, H, I, rows_of = MANY[name]
+    counts = np.array([rows_of(e) for e in range(E)])
+    rows, k = int(counts.sum()), 4
+    T = -(-rows // k)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)).cuda()
+    rng = np.random.default_rng(5)
+    tid = torch.from_numpy(rng.permutation(np.repeat(np.arange(T), k)[:rows]).astype(np.int32)).cuda()
+    print(f"{name}: E={E} H={H} I={I} T={T} rows={rows}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device="cuda").bfloat16()
+
+    x, w2, gate = normal(rows, I), normal(E, I, H), torch.rand(rows, generator=gen, device="cuda")
+    wl, _ = B.make_workload(T, H, I, E, k, 1, rows=rows)
+    ws = B.Workspace(B.workspace_size(wl))
+    out = torch.empty((T, H), device="cuda")
+
+    def stage(C):
+        out.fill_(float("nan"))
+        B.combine(x, w2, off, tid, gate, T=T, topk=k, num_consumers=C, out=out, workspace=ws)
+        return out.clone()
+
+    ref = stage(3)
+    for i in range(3):
+        assert torch.equal(stage(0), ref), i
+    assert torch.equal(stage(3), ref) and ws.status() == 0
+    del x, w2
+    hidden, w1 = normal(T, H), normal(E, H, 2 * I) * H ** -0.5
+    packed, ref = B.pack_w1(w1), torch.empty((rows, I), device="cuda")
+    bounds = off.tolist()
+    for e in range(E):
+        a, b = bounds[e], bounds[e + 1]
+        h = hidden[tid[a:b].long()].float() @ w1[e].float()
+        ref[a:b] = torch.nn.functional.silu(h[:, :I]) * h[:, I:]
+    for i in range(3):
+        got = B.gemm1_swiglu(hidden, packed, off, tid, k, rows)
+        # (the bound of test_up_projection_tiles)
+        assert (got.float() - ref).abs().le(2 ** -8 * ref.abs() + 2e-4).all(), i

@@ -35,3 +35,26 @@ result = launches()
             assert "gemm_kernel" in got[i - 1][0] and got[i - 1][3] == thread, got[i - 1:i + 1]
         elif "fill_zero" in kernel:
             assert "fill_zero" not in got[i + 1][0] and got[i + 1][3] == thread, got[i:i + 2]
+
+
+# E, H, I, T, topk: batches of full tiles with smaller ones for the rest
+LARGE = [(32, 2048, 704, 16384, 6), (30, 2048, 704, 8192, 4), (128, 4096, 1536, 4096, 8),
+         (1024, 512, 128, 16384, 8), (1024, 4096, 768, 32768, 8)]
+
+
+def test_workgroups_of_large_batches(recorder):
+    """One workgroup per CU for the up-projection's GEMM, and at most two more
+    per CU for the stage's: none is started to find out that there is nothing
+    for it to do."""
+    got = launch_recorder.run(recorder, f'''
+result = []
+for E, H, I, T, k in {LARGE}:
+    assert call("gemm1", T, H, I, E, k) == 0
+    assert call("combine", T, H, I, E, k) == 0
+    result.append(launches())
+''')
+    for shape, calls in zip(LARGE, got):
+        calls = [c for c in calls if "fill_zero" not in c[0]]
+        assert ["mixed_gemm" in c[0] for c in calls] == [True, True, False], shape
+        assert calls[0][1] == 256, (shape, calls[0])
+        assert 256 < calls[1][1] <= 3 * 256, (shape, calls[1])
