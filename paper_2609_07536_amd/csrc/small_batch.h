@@ -105,6 +105,69 @@ __device__ __forceinline__ uint32_t small_a_off(const G1Args& a, int r0, int row
 __device__ __forceinline__ int small_n(const KArgs& a) { return a.H; }
 __device__ __forceinline__ int small_n(const G1Args& a) { return 2 * a.I; }
 
+// The rows of 64 K experts from e0 on, K neighbouring ones in each lane, by one
+// round trip (with K = 1 alone, E = 1024 experts took a wave 16 of them: the
+// stage of H = 2048, I = 256, 16 rows each 574 us). Clamped as in load_experts;
+// experts past E are empty.
+template <int K>
+struct ExpertRows {
+  int start[K], count[K];
+  bool bad;   // this lane's offsets are not a non-decreasing prefix of [0, rows]
+  __device__ __forceinline__ ExpertRows(const int32_t* offsets, long long rows, int E, int e0) {
+    const int e = e0 + K * (threadIdx.x & 63), cap = (int)rows;
+    int off[K + 1];
+#pragma unroll
+    for (int i = 0; i <= K; ++i) off[i] = offsets[min(e + i, E)];
+    bad = e == 0 && off[0] != 0;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      bad |= off[i + 1] < off[i] || off[i + 1] > cap;
+      start[i] = min(max(off[i], 0), cap);
+      count[i] = max(min(off[i + 1], cap) - start[i], 0);   // (experts past E: off[i + 1] is off[i])
+    }
+  }
+  template <class Units>
+  __device__ __forceinline__ int sum(Units units) const {   // of this lane's experts
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < K; ++i) n += units(count[i]);
+    return n;
+  }
+};
+
+// An expert's rows, its first m-unit and how many it has.
+struct ExpertUnit {
+  int e, start, count, first, n;
+};
+// The expert that holds m-unit mt of the chunk at e0, which starts at m-unit
+// `carry`; v: the inclusive prefix of the lanes' sums.
+template <int K, class Units>
+__device__ __forceinline__ ExpertUnit find_expert(const ExpertRows<K>& r, int e0, int mt, Units units,
+                                                  int carry, int v) {
+  // the first lane whose prefix passes mt, and its expert that does
+  const int l = (int)__builtin_ctzll(__ballot(carry + v > mt));
+  int k = 0, first = carry + v - r.sum(units), start = r.start[0], count = r.count[0], n = units(count);
+#pragma unroll
+  for (int i = 1; i < K; ++i)
+    if (mt >= first + n) {
+      first += n;
+      k = i, start = r.start[i], count = r.count[i], n = units(count);
+    }
+  return {e0 + K * l + __builtin_amdgcn_readlane(k, l), __builtin_amdgcn_readlane(start, l),
+          __builtin_amdgcn_readlane(count, l), __builtin_amdgcn_readlane(first, l),
+          __builtin_amdgcn_readlane(n, l)};
+}
+
+__device__ __forceinline__ int wave_prefix(int v) {   // inclusive, over the lanes
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int u = __shfl_up(v, d);
+    if (lane >= d) v += u;
+  }
+  return v;
+}
+
 struct SmallUnit {
   int e, r0, rows_valid, n0;
   bool ok;
@@ -112,69 +175,60 @@ struct SmallUnit {
 
 // This workgroup's unit (expert -> n-tile -> m-tile; consecutive units of an
 // XCD are neighbours), by each wave for itself.
-template <int BM, int BN>
-__device__ __forceinline__ SmallUnit small_unit(const int32_t* offsets, long long rows, int E,
-                                                int NT, uint32_t* status, int* rows_dev) {
-  const int lane = threadIdx.x & 63;
-  int s = 0, cnt = 0, nm = 0, v = 0;
-  bool bad = false;
-  auto scan = [&](int e0) {   // lane's expert e0 + lane; v: inclusive m-tile prefix in the chunk
-    const int e = e0 + lane;
-    s = cnt = 0;
-    if (e < E) {
-      long long b = offsets[e], en = offsets[e + 1];
-      if ((e == 0 && b != 0) || en < b || en > rows) bad = true;
-      b = b < 0 ? 0 : (b > rows ? rows : b);
-      en = en < b ? b : (en > rows ? rows : en);
-      s = (int)b;
-      cnt = (int)(en - b);
-    }
-    nm = (cnt + BM - 1) / BM;
-    v = nm;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int u = __shfl_up(v, d);
-      if (lane >= d) v += u;
-    }
-  };
-  int total = 0, last = 0;
-  for (int e0 = 0; e0 < E; e0 += 64) {
-    scan(e0);
-    total += __builtin_amdgcn_readlane(v, 63);
-    last = __builtin_amdgcn_readlane(s + cnt, (E - 1) & 63);
+template <int BM, int BN, int K>
+__device__ __forceinline__ SmallUnit small_unit_of(const int32_t* offsets, long long rows, int E, int NT,
+                                                   uint32_t* status, int* rows_dev) {
+  constexpr int kChunk = 64 * K;
+  auto tiles = [](int count) { return (count + BM - 1) / BM; };
+  ExpertRows<K> r(offsets, rows, E, 0);
+  bool bad = r.bad;
+  int mine = r.sum(tiles), e0 = 0;
+  for (int e = kChunk; e < E; e += kChunk) {   // (the last chunk stays in r)
+    r = ExpertRows<K>(offsets, rows, E, e0 = e);
+    bad |= r.bad;
+    mine += r.sum(tiles);
   }
-  *rows_dev = last;
+  // the last row: the end of the last lane's last expert, empty or not
+  *rows_dev = __builtin_amdgcn_readlane(r.start[K - 1] + r.count[K - 1], 63);
   if (bad && blockIdx.x == 0)
     __hip_atomic_fetch_or(status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int v = wave_prefix(mine);
   SmallUnit u = {0, 0, 0, 0, false};
   const int b = blockIdx.x;
-  const long long units = (long long)total * NT;
+  const long long units = (long long)__builtin_amdgcn_readlane(v, 63) * NT;
   const long long chunk = (units + 7) >> 3;
   const long long unit = (long long)(b & 7) * chunk + (b >> 3);
   u.ok = (b >> 3) < chunk && unit < units;
   if (!u.ok) return u;
   const int mt = (int)(unit / NT);
-  int carry = 0, e0 = 0;
-  if (E > 64) {
-    for (;; e0 += 64) {
-      scan(e0);
+  int carry = 0;
+  if (E > kChunk) {
+    for (e0 = 0;; e0 += kChunk) {
+      r = ExpertRows<K>(offsets, rows, E, e0);
+      v = wave_prefix(r.sum(tiles));
       const int sum = __builtin_amdgcn_readlane(v, 63);
       if (mt < carry + sum) break;
       carry += sum;
+      u.ok = e0 + kChunk < E;   // (always: mt is below their sum)
+      if (!u.ok) return u;
     }
   }
-  // the lane whose expert holds m-tile mt: the first with prefix end > mt
-  const int j = (int)__builtin_ctzll(__ballot(carry + v > mt));
-  u.e = e0 + j;
-  const int first = carry + __builtin_amdgcn_readlane(v - nm, j);
-  const int n_m = __builtin_amdgcn_readlane(nm, j);
-  const int within = (int)(unit - (long long)first * NT);
-  const int nt = within / n_m;
-  const int mi = within - nt * n_m;
+  const ExpertUnit x = find_expert(r, e0, mt, tiles, carry, v);
+  const int within = (int)(unit - (long long)x.first * NT);
+  const int nt = within / x.n;
+  const int mi = within - nt * x.n;
+  u.e = x.e;
   u.n0 = nt * BN;
-  u.r0 = __builtin_amdgcn_readlane(s, j) + mi * BM;
-  u.rows_valid = min(BM, __builtin_amdgcn_readlane(cnt, j) - mi * BM);
+  u.r0 = x.start + mi * BM;
+  u.rows_valid = min(BM, x.count - mi * BM);
   return u;
+}
+template <int BM, int BN>
+__device__ __forceinline__ SmallUnit small_unit(const int32_t* offsets, long long rows, int E, int NT,
+                                                uint32_t* status, int* rows_dev) {
+  return E <= 64    ? small_unit_of<BM, BN, 1>(offsets, rows, E, NT, status, rows_dev)
+         : E <= 128 ? small_unit_of<BM, BN, 2>(offsets, rows, E, NT, status, rows_dev)
+                    : small_unit_of<BM, BN, 4>(offsets, rows, E, NT, status, rows_dev);
 }
 
 // The tile's Y rows, through each wave's own part of the ring to 64- or
@@ -520,39 +574,57 @@ __device__ __forceinline__ float mixed_time(int full, int small, int P, int fc, 
 
 // The plan with the least time, from the expert counts alone, so every wave
 // of the launch finds the same one.  Tile times for nk 64-deep stages, in
-// 10 ns (measured, 704 and 2048 deep: a full tile 1.5 us a stage + 4 us, a
-// smaller one 0.93 us a stage + 5.5 us, as it starts on its own).
+// 10 ns, measured: 704 and 2048 deep, a full tile 1.5 us a stage + 4 us, a
+// smaller one 0.93 us a stage + 5.5 us, as it starts on its own.  An expert of
+// one m-tile streams its weights from HBM for it alone: the stage (256 to 1536
+// deep, E = 512 and 1024) 1.66 us a stage + 1.5 us for a full tile and 1.28 us +
+// 4.5 us for a smaller one, the up-projection (512 to 4096 deep) 1.66 us + 5.5 us
+// and 1.36 us + 4.2 us.  So the stage's full tiles stay whole for such
+// experts below 8 stages: H = 2048, I = 256, E = 1024, 16 rows each, 284 us
+// against 328; I = 768 takes 640 with the smaller ones against 698.
 template <class Args>
 __device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
   const int lane = threadIdx.x & 63;
   const int N = small_n(a), nk = min(1024, (gemm_k(a) + kBK - 1) / kBK);
-  int all = 0, low = 0, mid = 0;   // m-tiles; experts with 1..128, 129..192 rows past them
-  for (int e0 = 0; e0 < a.E; e0 += 64) {
-    int cnt = 0;
-    if (e0 + lane < a.E) {
-      long long s = a.offsets[e0 + lane], en = a.offsets[e0 + lane + 1];
-      s = s < 0 ? 0 : (s > a.rows ? a.rows : s);
-      en = en < s ? s : (en > a.rows ? a.rows : en);
-      cnt = (int)(en - s);
+  // m-tiles; experts with 1..128, 129..192 rows past them, and those of one m-tile
+  int all = 0, low = 0, mid = 0, one = 0, one_low = 0, one_mid = 0;
+  auto count_tiles = [&](auto k) {
+    constexpr int K = decltype(k)::value;
+    for (int e0 = 0; e0 < a.E; e0 += 64 * K) {
+      const ExpertRows<K> r(a.offsets, a.rows, a.E, e0);
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        const int past = r.count[i] % kBM;
+        const u64 is_low = __ballot(past >= 1 && past <= 128), is_mid = __ballot(past >= 129 && past <= 192);
+        const u64 is_one = __ballot(r.count[i] >= 1 && r.count[i] <= kBM);
+        low += __builtin_popcountll(is_low);
+        mid += __builtin_popcountll(is_mid);
+        one += __builtin_popcountll(is_one);
+        one_low += __builtin_popcountll(is_low & is_one);
+        one_mid += __builtin_popcountll(is_mid & is_one);
+      }
+      all += r.sum([](int count) { return (count + kBM - 1) / kBM; });
     }
-    const int past = cnt % kBM;
-    low += __builtin_popcountll(__ballot(past >= 1 && past <= 128));
-    mid += __builtin_popcountll(__ballot(past >= 129 && past <= 192));
-    all += (cnt + kBM - 1) / kBM;
-  }
+  };
+  if (a.E <= 64)
+    count_tiles(std::integral_constant<int, 1>());
+  else
+    count_tiles(std::integral_constant<int, 4>());
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) all += __shfl_xor(all, d);
   all = __builtin_amdgcn_readfirstlane(all);
   // one round of full tiles holds everything (nothing to weigh: 3 us less)
   const int whole = (N + kBN - 1) / kBN;
   if (all <= small_div(P, whole)) return {kBM - 1, false, whole, all * whole, 0, 0, 0, 0};
-  const int fc = 150 * nk + 400, hc = 93 * nk + 550;
+  const int fc_far = RowGather<Args>::on ? 166 * nk + 550 : 166 * nk + 150;
+  const int hc_far = RowGather<Args>::on ? 136 * nk + 420 : 128 * nk + 450;
   // lane l weighs plan l: up to 192, 128 or no rows (l % 3) past an expert's
   // last full tile, with the edge tiles from l = 3 on
   const int p = lane % 3;
   const bool edge = lane >= 3;
   const int blocks = edge ? N / kBN : (N + kBN - 1) / kBN;
-  const int full = (all - (p == 0 ? low + mid : p == 1 ? low : 0)) * blocks;
+  const int m_full = all - (p == 0 ? low + mid : p == 1 ? low : 0);
+  const int full = m_full * blocks;
   const int bottoms = p == 0 ? low + 2 * mid : p == 1 ? low : 0;
   const int edges = edge ? all : 0;
   float cost = 3e38f;
@@ -561,6 +633,12 @@ __device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
   // (past 2^22 tiles, where small_div ends, only plan 2: full tiles alone)
   if (lane < (mixed_edge(N) ? 6 : 3) && full < (1 << 22) && small_all < (1 << 22)) {
     const int small = (int)small_all;
+    // mean times, by the share of the tiles whose experts have no other
+    const int one_full = one - (p == 0 ? one_low + one_mid : p == 1 ? one_low : 0);
+    const int one_small = (p == 0 ? one_low + 2 * one_mid : p == 1 ? one_low : 0) * blocks;
+    int fc = 150 * nk + 400, hc = 93 * nk + 550;
+    if (m_full > 0) fc += (int)((fc_far - fc) * ((float)one_full / m_full));
+    if (small > 0) hc += (int)((hc_far - hc) * ((float)one_small / small));
     // the average load breaks ties (and counts for the power it takes); the
     // smaller tiles have to save a sixth of a full one (one round of full tiles
     // for everything 35.6 us, with smaller ones on its idle CUs 39.7)
@@ -587,6 +665,38 @@ __device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
   plan.early = __builtin_amdgcn_readlane(early, best);
   plan.late = __builtin_amdgcn_readlane(late, best);
   return plan;
+}
+
+// The stage's first workgroup leaves the plan in the workspace, tagged with the
+// launch, for those behind the first P, which start later: one that finds it
+// needs no plan of its own, one that does not (nothing waits) makes it.  (Two
+// rounds of idle workgroups with plans of their own, H = 512, I = 128, E = 1024,
+// 16 rows each: 67 us, now 59.)
+__device__ __forceinline__ void leave_plan(const KArgs& a, const MixedPlan& plan, u64 epoch) {
+  const u64 tag = (u64)(uint32_t)epoch << 32;   // (its low half is never 0)
+  const uint32_t w[3] = {(uint32_t)plan.pad << 1 | plan.edge, (uint32_t)plan.edges, (uint32_t)plan.bottoms};
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    __hip_atomic_store(a.plan_left + i, tag | w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ MixedPlan find_plan(const KArgs& a, int P) {
+  const uint32_t tag = (uint32_t)launch_epoch(a);
+  u64 w[3];
+  bool all = true;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    w[i] = __hip_atomic_load(a.plan_left + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    all &= (uint32_t)(w[i] >> 32) == tag;
+  }
+  if (!__all(all)) return mixed_plan(a, P);
+  MixedPlan plan = {};
+  const int first = __builtin_amdgcn_readfirstlane((int)(uint32_t)w[0]);
+  plan.pad = first >> 1;
+  plan.edge = first & 1;
+  plan.blocks = plan.edge ? a.H / kBN : (a.H + kBN - 1) / kBN;
+  plan.edges = __builtin_amdgcn_readfirstlane((int)(uint32_t)w[1]);
+  plan.bottoms = __builtin_amdgcn_readfirstlane((int)(uint32_t)w[2]);
+  return plan;   // (full, early and late are the first P's)
 }
 
 // The smaller tiles that the up-projection's workgroup b of P takes, the first
@@ -661,60 +771,53 @@ struct MixedQueue {
 };
 
 // Unit `i` of the smaller tiles: edges first, then bottoms; by each wave for
-// itself.  (A negative i: none.)
-template <class Args>
-__device__ __forceinline__ SmallUnit mixed_unit(const Args& a, const MixedPlan& plan, int i) {
-  if (i < 0) return {0, 0, 0, 0, false};
-  const int lane = threadIdx.x & 63;
+// itself.
+template <int K, class Args>
+__device__ __forceinline__ SmallUnit mixed_unit_of(const Args& a, const MixedPlan& plan, int i, bool edge) {
   SmallUnit u = {0, 0, 0, 0, true};
-  const bool edge = i < plan.edges;
   const int per = edge ? 1 : plan.blocks;   // column blocks per m-unit
   const int unit = edge ? i : i - plan.edges;
   const int mt = unit / per;
-  int s = 0, cnt = 0, n = 0, v = 0, carry = 0, e0 = 0;
-  for (;; e0 += 64) {   // the chunk of 64 experts that holds m-unit mt
-    const int e = e0 + lane;
-    s = cnt = 0;
-    if (e < a.E) {
-      long long b = a.offsets[e], en = a.offsets[e + 1];
-      b = b < 0 ? 0 : (b > a.rows ? a.rows : b);
-      en = en < b ? b : (en > a.rows ? a.rows : en);
-      s = (int)b;
-      cnt = (int)(en - b);
-    }
-    n = edge ? (cnt + kBM - 1) / kBM : mixed_bottoms(cnt, plan.pad);
-    v = n;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int x = __shfl_up(v, d);
-      if (lane >= d) v += x;
-    }
+  auto units = [=](int count) { return edge ? (count + kBM - 1) / kBM : mixed_bottoms(count, plan.pad); };
+  for (int carry = 0, e0 = 0; e0 < a.E; e0 += 64 * K) {
+    const ExpertRows<K> r(a.offsets, a.rows, a.E, e0);
+    const int v = wave_prefix(r.sum(units));
     const int sum = __builtin_amdgcn_readlane(v, 63);
-    if (mt < carry + sum) break;
-    carry += sum;
+    if (mt >= carry + sum) {
+      carry += sum;
+      continue;
+    }
+    const ExpertUnit x = find_expert(r, e0, mt, units, carry, v);
+    const int within = unit - x.first * per;
+    const int nt = within / x.n, mi = within - nt * x.n;
+    const int row = edge ? mi * kBM : (x.count + plan.pad) / kBM * kBM + mi * MixedBottom::BM;
+    u.e = x.e;
+    u.r0 = x.start + row;
+    u.rows_valid = min(edge ? kBM : MixedBottom::BM, x.count - row);
+    u.n0 = edge ? plan.blocks * kBN : nt * kBN;
+    return u;
   }
-  const int l = (int)__builtin_ctzll(__ballot(carry + v > mt));
-  u.e = e0 + l;
-  const int first = carry + __builtin_amdgcn_readlane(v - n, l);
-  const int n_m = __builtin_amdgcn_readlane(n, l);
-  const int within = unit - first * per;
-  const int nt = within / n_m, mi = within - nt * n_m;
-  const int count = __builtin_amdgcn_readlane(cnt, l);
-  const int row = edge ? mi * kBM : (count + plan.pad) / kBM * kBM + mi * MixedBottom::BM;
-  u.r0 = __builtin_amdgcn_readlane(s, l) + row;
-  u.rows_valid = min(edge ? kBM : MixedBottom::BM, count - row);
-  u.n0 = edge ? plan.blocks * kBN : nt * kBN;
+  u.ok = false;   // (never: i is below the plan's units)
   return u;
 }
+// (a negative i: none)
+template <class Args>
+__device__ __forceinline__ SmallUnit mixed_unit(const Args& a, const MixedPlan& plan, int i) {
+  if (i < 0) return {0, 0, 0, 0, false};
+  const bool edge = i < plan.edges;
+  return a.E <= 64 ? mixed_unit_of<1>(a, plan, i, edge) : mixed_unit_of<4>(a, plan, i, edge);
+}
 
-__device__ __forceinline__ void mixed_prologue(Smem& sm, const KArgs& a) {
+__device__ __forceinline__ void mixed_prologue(Smem& sm, const KArgs& a, const MixedPlan& plan) {
   if (threadIdx.x == 0) {
     sm.epoch = launch_epoch(a);   // load_experts synchronises
-    if (blockIdx.x == 0)
+    if (blockIdx.x == 0) {
       __hip_atomic_store(a.map_epoch, sm.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      leave_plan(a, plan, sm.epoch);
+    }
   }
 }
-__device__ __forceinline__ void mixed_prologue(Smem&, const G1Args&) {}
+__device__ __forceinline__ void mixed_prologue(Smem&, const G1Args&, const MixedPlan&) {}
 __device__ __forceinline__ void mixed_inverse_map(const Smem& sm, const KArgs& a) {
   consumer_prologue(sm, a, (long long)sm.start[a.E - 1] + sm.count[a.E - 1], false, a.P, false);
   waitcnt_vm<0>();   // nothing the compiler tracks stays in flight in the tile loop
@@ -761,7 +864,7 @@ mixed_gemm_kernel(Args a) {
   const int P = a.P;
   if constexpr (!kUp) {
     if ((int)blockIdx.x >= P) {
-      const MixedPlan plan = mixed_plan(a, P);
+      const MixedPlan plan = find_plan(a, P);
       MixedQueue queue(a, plan, (int)blockIdx.x - P);
       mixed_small_tiles(sm, a, plan, queue);
       return;
@@ -779,7 +882,7 @@ mixed_gemm_kernel(Args a) {
     else
       kept_share = {0, 0, 0, 0};
   }
-  mixed_prologue(sm, a);
+  mixed_prologue(sm, a, plan);
   load_experts(sm, a, plan.pad);
   a.ntps = plan.blocks;   // for decode_tile
   const int total = sm.tile_prefix[a.E] * a.ntps;
