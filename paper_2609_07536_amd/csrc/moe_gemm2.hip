@@ -118,8 +118,6 @@ struct KArgs {
   u64* map_epoch;             // two launches: the epoch the first built the inverse map with
   u64* over_cnt;              // two launches in mode 1: launch-tagged count of the rows past topk
                               // of their token, listed behind the inverse map (overflow_row)
-  u64* unit_ctr;              // two launches: [8] launch-tagged count of the smaller tiles an
-                              // XCD's workgroups have taken
   u64* plan_left;             // two launches: [3] the GEMM's plan, launch-tagged
   uint32_t* done_ctr;         // workgroups of this launch that have finished
   uint32_t* start_ctr;        // workgroups of this launch that have started
@@ -1983,8 +1981,7 @@ bool make_layout(const moe_workload_t* wl, Layout* L) {
                      // 256..319: per-split consumer task counters;
                      // 320: launch epoch (u64); 328: finished workgroups;
                      // 332: started workgroups; 336: the two launches' map epoch
-                     // (u64), 344: mode 1's overflow count (u64) and 352..415:
-                     // the smaller tiles taken on each XCD (u64 each); 416..439:
+                     // (u64), 344: mode 1's overflow count (u64) and 352..375:
                      // the GEMM's plan
   off += 512;
   L->wg_flags = off;
@@ -2572,8 +2569,7 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
   a.epoch_word = reinterpret_cast<u64*>(ws + L.status + 320);
   a.map_epoch = reinterpret_cast<u64*>(ws + L.status + 336);
   a.over_cnt = reinterpret_cast<u64*>(ws + L.status + 344);
-  a.unit_ctr = reinterpret_cast<u64*>(ws + L.status + 352);
-  a.plan_left = reinterpret_cast<u64*>(ws + L.status + 416);
+  a.plan_left = reinterpret_cast<u64*>(ws + L.status + 352);
   a.done_ctr = reinterpret_cast<uint32_t*>(ws + L.status + 328);
   a.start_ctr = reinterpret_cast<uint32_t*>(ws + L.status + 332);
   a.y_keep = 0;

@@ -506,21 +506,21 @@ __global__ void __launch_bounds__(C::kThr) small_gemm_kernel(Args a) {
 //    most 128 columns (2 I = 1408 is five blocks and a half);
 //  * 128 x 256 tiles over the rows past each expert's last full tile.
 // The stage starts further workgroups for those, 2 P at most, as the CUs become
-// free; each takes some by its index and then others from a counter per XCD in
-// the workspace.  The up-projection, whose workspace other calls may share,
-// gives each of its P workgroups as many, after its full tiles, as the plan says
-// for one with and one without a tile of the last round.  (With a workgroup
-// for every smaller tile that the host's bound allows, most found out for
-// themselves, on a CU of their own, that there was nothing for them: T =
-// 16384, H = 2048, I = 704, E = 32, up-projection 531.8 us, now 520.7, and E =
-// 1024, H = 512, I = 128, T = 16384 146 / 108.  In fixed shares the stage too
-// waits for a full tile's stores before the first smaller one: 388.4 us against
-// 383.3.)
+// free.  The up-projection gives each of its P workgroups as many, after its full
+// tiles, as the plan says for one with and one without a tile of the last round.
+// (With a workgroup for every smaller tile that the host's bound allows, most
+// found out for themselves, on a CU of their own, that there was nothing for
+// them: T = 16384, H = 2048, I = 704, E = 32, up-projection 531.8 us, now 520.7,
+// and E = 1024, H = 512, I = 128, T = 16384 146 / 108.  The stage's P workgroups
+// wait for a full tile's stores before the first smaller one: 388.4 us against
+// 383.3 with further ones, which start meanwhile.  Handed out by counters in the
+// workspace, the smaller tiles waited for the counters: H = 2048, I = 512, E =
+// 256, top-8, T = 8192, Zipf 1.0, 306 us, by index 280.)
 using MixedEdge = SmallTile<256, 128, 8, 2, 3>;
 using MixedBottom = SmallTile<128, 256, 8, 4, 3>;
-static_assert(offsetof(Smem, task) >= MixedEdge::S * MixedEdge::kSlot * 2 &&
-                  offsetof(Smem, task) >= MixedBottom::S * MixedBottom::kSlot * 2,
-              "the smaller tiles' rings lie over Smem, but not over what hands them out");
+static_assert(sizeof(Smem) >= MixedEdge::S * MixedEdge::kSlot * 2 &&
+                  sizeof(Smem) >= MixedBottom::S * MixedBottom::kSlot * 2,
+              "the smaller tiles' rings overlay the whole of Smem");
 
 // How a launch's rows and columns are cut: an expert has (count + pad) / 256
 // full m-tiles, the rows left are bottoms; `edge`: the last column block is
@@ -699,20 +699,20 @@ __device__ __forceinline__ MixedPlan find_plan(const KArgs& a, int P) {
   return plan;   // (full, early and late are the first P's)
 }
 
-// The smaller tiles that the up-projection's workgroup b of P takes, the first
-// full % P of which have a tile of the last round: first, first + step, ...
-// below end, `count` at most.  Each XCD (b mod 8) has a range of neighbouring
-// units, as long as its workgroups' share of the whole; those without a last
-// full tile take its front in turns, the others its back.
+// A workgroup's smaller tiles: first, first + step, ... below end, `count` at
+// most.
 struct MixedShare {
   int first, step, count, end;
-  __device__ __forceinline__ int ahead() {
+  __device__ __forceinline__ int next() {   // -1 at the end
     const int j = first;
     first += step;
     return count-- > 0 && j < end ? j : -1;
   }
-  __device__ __forceinline__ int claim(Smem&, const G1Args&) const { return -1; }
 };
+// Those of the up-projection's workgroup b of P, the first full % P of which
+// have a tile of the last round.  Each XCD (b mod 8) has a range of neighbouring
+// units, as long as its workgroups' share of the whole; those without a last
+// full tile take its front in turns, the others its back.
 __device__ __forceinline__ MixedShare mixed_share(const MixedPlan& plan, int b, int P) {
   const int rem = plan.full % P;
   const int units = plan.edges + plan.bottoms * plan.blocks;
@@ -735,40 +735,15 @@ __device__ __forceinline__ MixedShare mixed_share(const MixedPlan& plan, int b, 
   return sh;
 }
 
-// The smaller tiles that the stage's i-th workgroup behind the first P takes:
-// of its XCD's (i mod 8) eighth of the units [lo, lo + units) those by its index,
-// known ahead, for all but the last two rounds of the `per` workgroups there
-// (one round at least), then what a launch-tagged counter gives.  (sm.task lies
-// past the rings.)
-struct MixedQueue {
-  int lo, units, per, given, j;
-  __device__ __forceinline__ MixedQueue(const KArgs& a, const MixedPlan& plan, int i) {
-    const int all = plan.edges + plan.bottoms * plan.blocks, chunk = (all + 7) >> 3;
-    lo = (i & 7) * chunk;
-    units = max(0, min(chunk, all - lo));
-    per = ((int)gridDim.x - a.P) >> 3;   // (a multiple of eight workgroups)
-    given = max(units / per - 2, 1) * per;
-    j = i >> 3;
-  }
-  __device__ __forceinline__ int ahead() {   // by index
-    const int k = j;
-    j += per;
-    return k < given && k < units ? lo + k : -1;
-  }
-  __device__ __forceinline__ int claim(Smem& sm, const KArgs& a) const {   // from the counter
-    if (given >= units) return -1;
-    if (threadIdx.x == 0) {
-      u64* ctr = a.unit_ctr + ((blockIdx.x - a.P) & 7);
-      const u64 tag = (launch_epoch(a) & ((1ull << (64 - kCntBits)) - 1)) << kCntBits;
-      __hip_atomic_fetch_max(ctr, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const u64 n = __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      sm.task = (int)min(n & kCntMask, (u64)(units - given));
-    }
-    __syncthreads();
-    const int k = given + __builtin_amdgcn_readfirstlane(sm.task);
-    return k < units ? lo + k : -1;
-  }
-};
+// The smaller tiles that the stage's i-th workgroup behind the first P takes: of
+// its XCD's (i mod 8) eighth of the units those of its index, one in each round
+// of the `per` workgroups there.
+__device__ __forceinline__ MixedShare mixed_behind(const KArgs& a, const MixedPlan& plan, int i) {
+  const int all = plan.edges + plan.bottoms * plan.blocks, chunk = (all + 7) >> 3;
+  const int lo = (i & 7) * chunk;
+  const int per = ((int)gridDim.x - a.P) >> 3;   // (a multiple of eight workgroups)
+  return {lo + (i >> 3), per, chunk, min(lo + chunk, all)};
+}
 
 // Unit `i` of the smaller tiles: edges first, then bottoms; by each wave for
 // itself.
@@ -824,23 +799,21 @@ __device__ __forceinline__ void mixed_inverse_map(const Smem& sm, const KArgs& a
 }
 __device__ __forceinline__ void mixed_inverse_map(const Smem&, const G1Args&) {}
 
-// The smaller tiles of a workgroup, the ring over sm up to sm.task: those that
-// queue.ahead() gives, then those of queue.claim() (-1 at the end of each).  A
-// tile that is known ahead is looked up while the one before fills its ring:
-// after that one's epilogue the offsets' loads would wait for its stores.
-// (Every wave of the workgroup is past its use of sm on entry; the barrier keeps
-// a tile's loads behind the one before.)
-template <class Args, class Queue>
+// The smaller tiles of a workgroup's share, the ring over sm.  The next one is
+// looked up while a tile fills its ring: after its epilogue the offsets' loads
+// would wait for its stores.  (Every wave of the workgroup is past its use of sm
+// on entry; the barrier keeps a tile's loads behind the one before.)
+template <class Args>
 __device__ __forceinline__ void mixed_small_tiles(Smem& sm, const Args& a, const MixedPlan& plan,
-                                                  Queue& queue) {
+                                                  MixedShare share) {
   uint16_t* ring = reinterpret_cast<uint16_t*>(&sm);
-  int j = queue.ahead();
+  int j = share.next();
   SmallUnit u = mixed_unit(a, plan, j);
   while (u.ok) {
     const bool edge = j < plan.edges;
     SmallUnit u_next;
     auto look_up = [&] {
-      j = queue.ahead();
+      j = share.next();
       u_next = mixed_unit(a, plan, j);
     };
     if (edge)
@@ -848,10 +821,6 @@ __device__ __forceinline__ void mixed_small_tiles(Smem& sm, const Args& a, const
     else
       small_tile<MixedBottom>(a, ring, u, look_up);
     block_barrier();
-    if (!u_next.ok) {
-      j = queue.claim(sm, a);
-      u_next = mixed_unit(a, plan, j);
-    }
     u = u_next;
   }
 }
@@ -865,8 +834,7 @@ mixed_gemm_kernel(Args a) {
   if constexpr (!kUp) {
     if ((int)blockIdx.x >= P) {
       const MixedPlan plan = find_plan(a, P);
-      MixedQueue queue(a, plan, (int)blockIdx.x - P);
-      mixed_small_tiles(sm, a, plan, queue);
+      mixed_small_tiles(sm, a, plan, mixed_behind(a, plan, (int)blockIdx.x - P));
       return;
     }
   }
@@ -922,7 +890,7 @@ mixed_gemm_kernel(Args a) {
   }
   if constexpr (kUp) {
     const MixedPlan rest = kept_plan;
-    MixedShare share = kept_share;
+    const MixedShare share = kept_share;
     waitcnt_vm<63>();   // (these reads; its own loads compute_tile has waited for)
     block_barrier();
     mixed_small_tiles(sm, a, rest, share);

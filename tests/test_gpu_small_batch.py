@@ -166,7 +166,7 @@ def test_up_projection_tiles(gpu_lib, name):
 
 
 # E, H, I, rows of expert e: many more smaller tiles than CUs, so that a
-# workgroup takes several (by its index and from the counter; in fixed shares),
+# workgroup takes several (by its index, or in fixed shares),
 # with and without a narrower last column block
 MANY = {
     "bottoms": (300, 2048, 1040, lambda e: 30 + e % 31),
