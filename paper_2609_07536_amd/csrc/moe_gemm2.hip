@@ -2384,26 +2384,36 @@ hipError_t launch_mixed_gemm(Args a, const DevInfo& d, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Row tiles of an average routing (half a tile of padding per expert), times
-// 2 tile.
+// Row tiles of an average routing (half a tile of padding per expert, one tile
+// at least), times 2 tile.
 long long expected_rows(long long rows, int E, int tile) {
   const long long n = E < rows ? E : rows;
-  return 2 * rows + tile * n;
+  const long long padded = 2 * rows + tile * n, one_each = 2LL * tile * n;
+  return padded > one_each ? padded : one_each;
 }
+long long column_blocks(int N) { return (N + kBN - 1) / kBN; }
 // 256 x 256 tiles of an average routing over N columns.
 long long expected_tiles(long long rows, int E, int N) {
-  return expected_rows(rows, E, kBM) * ((N + kBN - 1) / kBN) / (2 * kBM);
+  return expected_rows(rows, E, kBM) * column_blocks(N) / (2 * kBM);
 }
 
-// The stage's grouped GEMM runs as small tiles up to two 256 x 256 tiles per
-// CU (three for reductions of 640 and more), beyond that as full tiles with
-// smaller ones for the rest.  Measured (us for the stage, small / full,
-// inputs changing from call to call): I = 704, H = 2048: 2.4 tiles per CU (E
-// = 30, top-4, T = 4096) 87.2 / 93.1, 2.75 (E = 32, top-6, T = 3072) 90.5 /
-// 97.3, 3.5 (T = 4096) 120.6 / 116.8; I = 512, H = 1024: 1.1 (E = 8, top-2,
-// T = 8192) 45.5 / 49, 2.1 (T = 16384) 84.3 / 82.0, 2.25 (E = 32, top-8, T =
-// 4096) 73.3 / 70.5.
+// The stage's grouped GEMM runs as small tiles
+//  * where an expert has 128 rows at most on average, up to six 256 x 256 tiles
+//    (however empty) per CU and 256 experts;
+//  * else up to two such tiles per CU (three for reductions of 640 and more);
+// beyond that as full tiles with smaller ones for the rest.  Measured (us for
+// the stage, small / full, inputs changing from call to call): I = 704, H =
+// 2048: 2.4 tiles per CU (E = 30, top-4, T = 4096) 87.2 / 93.1, 2.75 (E = 32,
+// top-6, T = 3072) 90.5 / 97.3, 3.5 (T = 4096) 120.6 / 116.8; I = 512, H =
+// 1024: 1.1 (E = 8, top-2, T = 8192) 45.5 / 49, 2.1 (T = 16384) 84.3 / 82.0,
+// 2.25 (E = 32, top-8, T = 4096) 73.3 / 70.5.  Few rows, 16 and 100 per expert:
+// H = 2048, I = 256, E = 128 (4 tiles per CU) 35 / 44 and 57 / 62, H = 4096,
+// I = 1536, E = 96 (6) 235 / 245 and 256 / 288, H = 2048, I = 768, E = 256 (8)
+// 178 / 184 and 211 / 242, I = 256 80 / 83 and 107 / 112, E = 512 (16) 178 /
+// 151 and 223 / 210, H = 512, I = 128, E = 512 (4) 39 / 35 and 53 / 53.
 bool small_stage(long long rows, int E, int H, int I, int cus) {
+  const long long n = E < rows ? E : rows;
+  if (rows <= 128 * n) return E <= 256 && n * column_blocks(H) <= 6LL * cus;
   return expected_tiles(rows, E, H) <= (I >= 640 ? 3LL : 2LL) * cus;
 }
 
@@ -2433,25 +2443,41 @@ hipError_t launch_combine(const KArgs& a, int cus, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The up-projection in 80ths of the time one full tile takes: small tiles
-// 50 while two per CU hold all of them, then 28 + 25 per 128 x 128 tile and
-// CU (23 where the full tiles leave an edge); full tiles with smaller ones
-// for the rest 82 while one per CU holds them, then 64 + 80 per 256 x 256
-// tile's work and CU.  Fitted to (us, small / full): H = 2048, I = 704, E =
-// 32, T = 512 33.5 / 53, 1024 60 / 55, 2048 89 / 90, 3072 118 / 127.5, 4096
-// 156 / 148, 8192 312 / 260, E = 30, top-4, T = 1024 48.5 / 63.6; H = 1024, I = 512, E = 32, T =
-// 800 29.9 / 31.8, 2048 50.2 / 54.1, 4096 85.8 / 88.7; H = 1352, I = 336, E =
-// 11, T = 2048 26.4 / 38.9, 8192 66.5 / 81.
+// The up-projection runs as small tiles
+//  * where an expert has 64 rows at most on average, up to 9/4 256 x 256 tiles
+//    (however empty) per CU: the time is the weights', and 64 x 128 tiles even
+//    out the rounds;
+//  * where one round of full tiles holds about everything (9/8 of one: the rows
+//    past a full tile are few), while two small tiles per CU hold about all of
+//    them (33/16), or with reductions up to 1024;
+//  * else by an estimate in 80ths of the time one full tile takes: small tiles
+//    28 + 25 per 128 x 128 tile and CU (23 where the full tiles leave an edge);
+//    full tiles with smaller ones for the rest 64 + 80 per 256 x 256 tile's work
+//    and CU.
+// Measured (us, small / full, inputs changing from call to call): H = 2048, I =
+// 704, 6 rows per expert: E = 64 63.5 / 79.6, 96 (9/4 tiles per CU) 106 / 120,
+// I = 768, E = 128, 16 rows 154 / 151.  One round: H = 2048, I = 704, E = 32,
+// top-6, T = 512 47.5 / 60.1, 700 71.7 / 63.5 (Zipf 0.8: 67.7 / 67.4), 1024
+// 73 / 64.6, 1300 (9/8) 78.5 / 68.1 (Zipf 1.2: 78.1 / 78.7), E = 30, top-4, T = 900
+// 49.7 / 61.8, 1024 (33/16) 72.2 / 63.3, Zipf 0.8 50.7 / 67.5 and 1.2 71.1 / 66.7 (as
+// the experts leave more or fewer tiles than two per CU), 1300 68.9 /
+// 63.4, 2048 (9/8) 83.7 / 77.3; H = 4096, I = 1792, E = 8, T =
+// 1300 123.6 / 108.1; H = 1024, I = 512, E = 32, T = 1300 31.1 / 33.0, 1600
+// (9/8) 34.6 / 34.6.  More: H = 2048, I = 704, E = 32, T = 1600 89.9 / 101.9, 2048
+// 102.5 / 104.2, 2700 123.6 / 122.5, 5000 190.8 / 181.3, 8192 292 / 276; H =
+// 1024, I = 512, E = 32, T = 2048 49.9 / 52.0, 3700 71.5 / 68.7 (Zipf 1.0: 72.1 /
+// 76.9), 8192 153 / 150; H = 1352, I = 336, E = 11, T = 8192 63.3 / 76.6.
 bool small_up_projection(const G1Args& a, int cus) {
   const int N = a.nsplit;
+  const long long n = a.E < a.rows ? a.E : a.rows;
+  if (a.rows <= 64 * n) return n * column_blocks(N) * 4 <= 9LL * cus;
   // columns computed: whole blocks of 256, but 128 where an edge has its tiles
   const int width = mixed_edge(N) ? kEdge : kBN;
   const long long cols = (N + width - 1) / width * width;
   const long long units = expected_rows(a.rows, a.E, 128) * (cols / 128) / 256;
-  const long long small = units <= 2LL * cus ? 50LL * cus
-                                             : 28LL * cus + (width == kEdge ? 23 : 25) * units;
-  const long long full = expected_tiles(a.rows, a.E, N) <= cus
-                             ? 82LL * cus : 64LL * cus + 80 * (a.rows * cols / (kBM * kBN));
+  if (expected_tiles(a.rows, a.E, N) * 8 <= 9LL * cus) return units * 16 <= 33LL * cus || a.H <= 1024;
+  const long long small = 28LL * cus + (width == kEdge ? 23 : 25) * units;
+  const long long full = 64LL * cus + 80 * (a.rows * cols / (kBM * kBN));
   return small < full;
 }
 

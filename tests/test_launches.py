@@ -58,3 +58,38 @@ for E, H, I, T, k in {LARGE}:
         assert ["mixed_gemm" in c[0] for c in calls] == [True, True, False], shape
         assert calls[0][1] == 256, (shape, calls[0])
         assert 256 < calls[1][1] <= 3 * 256, (shape, calls[1])
+
+
+# E, H, I, T, topk and which tiles they run as: the sizes at each limit of the
+# rules, and many experts with few rows
+ROUTES = {
+    "gemm1": [
+        (32, 2048, 704, 64, 6, "small"), (64, 2048, 704, 64, 6, "small"), (96, 2048, 704, 64, 6, "small"),
+        (128, 2048, 704, 64, 6, "mixed"), (1024, 2048, 768, 64, 8, "mixed"), (8, 4096, 14336, 8, 2, "mixed"),
+        # one round of full tiles: more than two small tiles per CU, a longer reduction
+        (32, 2048, 704, 650, 6, "small"), (32, 2048, 704, 700, 6, "mixed"), (32, 2048, 704, 1300, 6, "mixed"),
+        (30, 2048, 704, 1024, 4, "small"), (30, 2048, 704, 1300, 4, "mixed"), (32, 1024, 512, 1300, 8, "small"),
+        (32, 2048, 704, 1600, 6, "small"), (32, 2048, 704, 8192, 6, "mixed"), (11, 1352, 336, 8192, 3, "small"),
+    ],
+    "combine": [
+        (32, 2048, 704, 64, 6, "small"), (128, 2048, 256, 256, 8, "small"), (256, 1024, 256, 512, 8, "small"),
+        (96, 4096, 1536, 192, 8, "small"), (128, 4096, 1536, 256, 8, "mixed"), (512, 512, 128, 1024, 8, "mixed"),
+        (128, 2048, 256, 2048, 8, "small"), (128, 2048, 256, 2056, 8, "mixed"),
+        (30, 2048, 704, 4096, 4, "small"), (32, 2048, 704, 4096, 6, "mixed"), (8, 1024, 512, 8192, 2, "small"),
+    ],
+}
+
+
+@pytest.mark.parametrize("op", list(ROUTES))
+def test_tiles_by_batch(recorder, op):
+    """The rule that chooses between small tiles and full ones counts what both
+    would run: it does not turn to full tiles because near-empty experts are
+    many, nor to small ones where one round of full tiles is faster."""
+    shapes = [s[:5] for s in ROUTES[op]]
+    got = launch_recorder.run(recorder, f'''
+result = []
+for E, H, I, T, k in {shapes}:
+    assert call("{op}", T, H, I, E, k) >= 0
+    result.append([c[0] for c in launches() if "fill_zero" not in c[0]][0])
+''')
+    assert [g.split("_gemm_kernel")[0] for g in got] == [s[5] for s in ROUTES[op]], got
