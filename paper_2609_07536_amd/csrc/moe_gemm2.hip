@@ -39,6 +39,7 @@
 #include <cstring>
 #include <mutex>
 #include <random>
+#include <type_traits>
 #include <unordered_map>
 
 #include "moe_gemm2.h"
@@ -444,20 +445,85 @@ __device__ void load_experts(Smem& sm, const Args& a, int pad = kBM - 1) {
   __syncthreads();
 }
 
-// A row past its token's topk.  The owner-write modes drop and flag it; mode 1
-// adds every row, so there it goes to a list (of less than T topk rows: that
-// path runs only with rows <= T topk) after the inverse map's T topk slots.
-__device__ __forceinline__ void overflow_row(const KArgs& a, int r, u64 cnt_epoch) {
+// A row past its token's topk (it took `slot`).  The owner-write modes drop and
+// flag it; mode 1 adds every row, so there it goes to a list (of less than T topk
+// rows: that path runs only with rows <= T topk) after the inverse map's T topk
+// slots, and the token's first such row zeroes the token's output, to which the
+// second launch then adds.  The lanes here take their places by one atomic.
+__device__ __forceinline__ void overflow_row(const KArgs& a, int r, int t, uint32_t slot, u64 cnt_epoch) {
   if (a.mode != 1) {
     __hip_atomic_fetch_or(a.status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
-  __hip_atomic_fetch_max(a.over_cnt, cnt_epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const u64 old = __hip_atomic_fetch_add(a.over_cnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const u64 here = __ballot(1);
+  const int before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(here >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)here, 0u));
+  u64 old = 0;
+  if (before == 0) {
+    __hip_atomic_fetch_max(a.over_cnt, cnt_epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    old = __hip_atomic_fetch_add(a.over_cnt, (u64)__builtin_popcountll(here), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+  }
   const long long slots = (long long)a.T * a.topk;
-  const long long i = (long long)(old & kCntMask);
+  const long long i = (long long)((uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)old) & kCntMask) + before;
   if (i < slots) a.inv[slots + i] = r;
+  if (slot == (uint32_t)a.topk) {
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    f32x4* o = (f32x4*)(a.out + (size_t)t * a.H);
+    for (int c = 0; c < a.H / 4; ++c) o[c] = z;
+  }
 }
+
+// A row's place among its token's rows: the launch-tagged count it found, by an
+// atomic max, which opens the launch's count (a counter from an older launch
+// holds a smaller epoch in its high word), and an add.  The two atomics of a
+// thread on one address are performed in order, so the add always sees this
+// epoch; no compare-and-swap, no dependent round trip.
+// Mode 1 allows a token any number of rows, and lanes on one counter wait for
+// each other (half of 65536 rows: 810 us): there lanes with the same token as one
+// of four sampled lanes take their places by that token's first lane.
+struct RowPlace {
+  u64 old = 0;
+  int lead = 0, rank = 0;   // the lane that took the place, and how far after it this one is
+  __device__ __forceinline__ void take(const KArgs& a, int t, u64 cnt_epoch) {
+    const int lane = threadIdx.x & 63;
+    lead = lane;
+    rank = 0;
+    int n = 1;
+    if (a.mode == 1) {
+      u64 left = __ballot(1);
+#pragma unroll
+      for (int s = 0; s < 64; s += 16) {
+        if (!(left >> s & 1)) continue;
+        const u64 same = __ballot(t == __builtin_amdgcn_readlane(t, s)) & left;
+        if (same >> lane & 1) {
+          lead = (int)__builtin_ctzll(same);
+          rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32),
+                                                __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+          n = lane == lead ? (int)__builtin_popcountll(same) : 0;
+        }
+        left &= ~same;
+      }
+    }
+    if (n > 0) {
+      __hip_atomic_fetch_max(&a.tok_cnt[t], cnt_epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      old = __hip_atomic_fetch_add(&a.tok_cnt[t], (u64)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  // row r of token t to its place (by the same lanes as take)
+  __device__ __forceinline__ void place(const KArgs& a, int r, int t, u64 cnt_epoch) {
+    if (a.mode == 1) {
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * lead, (int)(uint32_t)old);
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * lead, (int)(uint32_t)(old >> 32));
+      old = ((u64)hi << 32 | lo) + (u64)rank;
+    }
+    const uint32_t slot = (old & ~kCntMask) == cnt_epoch ? (uint32_t)(old & kCntMask) : 0xffffffffu;
+    if (slot >= (uint32_t)a.topk)
+      overflow_row(a, r, t, slot, cnt_epoch);
+    else
+      a.inv[(long long)t * a.topk + slot] = (int32_t)r;
+  }
+};
 
 // What the consumers need before their first task, built by every
 // workgroup for its share: for the owner-write combine, the rows of each
@@ -487,19 +553,9 @@ __device__ void consumer_prologue(const Smem& sm, const KArgs& a, long long rows
       __hip_atomic_fetch_or(a.status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       continue;
     }
-    // Open this launch's count (a counter from an older launch holds a
-    // smaller epoch in its high word), then take a slot.  The two atomics
-    // of a thread on one address are performed in order, so the add always
-    // sees this epoch; no compare-and-swap, no dependent round trip.
-    __hip_atomic_fetch_max(&a.tok_cnt[t], cnt_epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const u64 old = __hip_atomic_fetch_add(&a.tok_cnt[t], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t slot =
-        (old & ~kCntMask) == cnt_epoch ? (uint32_t)(old & kCntMask) : 0xffffffffu;
-    if (slot >= (uint32_t)a.topk) {
-      overflow_row(a, (int)r, cnt_epoch);
-      continue;
-    }
-    a.inv[(long long)t * a.topk + slot] = (int32_t)r;
+    RowPlace p;
+    p.take(a, t, cnt_epoch);
+    p.place(a, (int)r, t, cnt_epoch);
   }
   // workgroup 0 resets the consumer task counters; every claim of split s
   // comes after the claimer has seen workgroup 0's release (its inverse-map
@@ -2434,12 +2490,19 @@ hipError_t launch_combine(const KArgs& a, int cus, hipStream_t s) {
   const long long blocks = (units + kSmallCombineWaves - 1) / kSmallCombineWaves;
   const dim3 grid((unsigned)(blocks < kMaxSmallGrid ? blocks : kMaxSmallGrid));
   const dim3 block(kSmallCombineWaves * 64);
-  if (!a.y_keep)
-    hipLaunchKernelGGL((small_combine_kernel<2, true>), grid, block, 0, s, a);
-  else if (wide)
-    hipLaunchKernelGGL((small_combine_kernel<2, false>), grid, block, 0, s, a);
+  auto launch = [&](auto scatter) {
+    constexpr bool kScatter = decltype(scatter)::value;
+    if (!a.y_keep)
+      hipLaunchKernelGGL((small_combine_kernel<2, true, kScatter>), grid, block, 0, s, a);
+    else if (wide)
+      hipLaunchKernelGGL((small_combine_kernel<2, false, kScatter>), grid, block, 0, s, a);
+    else
+      hipLaunchKernelGGL((small_combine_kernel<1, false, kScatter>), grid, block, 0, s, a);
+  };
+  if (a.mode == 1)
+    launch(std::true_type());
   else
-    hipLaunchKernelGGL((small_combine_kernel<1, false>), grid, block, 0, s, a);
+    launch(std::false_type());
   return hipGetLastError();
 }
 

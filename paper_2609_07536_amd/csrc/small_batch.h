@@ -301,7 +301,8 @@ __device__ __forceinline__ void small_store(const G1Args& a, f32x16 (&acc)[C::NB
 // out before the operand loads, and their results are used after the unit.
 template <int kThr>
 struct RowShare {
-  u64 epoch = 0, cnt_epoch = 0, slot_word = 0;
+  u64 epoch = 0, cnt_epoch = 0;
+  RowPlace mine;
   int per = 0, row = -1, tok = -1;
 
   __device__ __forceinline__ void load(const KArgs& a) {
@@ -321,18 +322,6 @@ struct RowShare {
     __hip_atomic_fetch_or(a.status, kStBadRouting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return false;
   }
-  __device__ __forceinline__ u64 take(const KArgs& a, int t) {
-    __hip_atomic_fetch_max(&a.tok_cnt[t], cnt_epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return __hip_atomic_fetch_add(&a.tok_cnt[t], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __device__ __forceinline__ void place(const KArgs& a, int r, int t, u64 old) {
-    const uint32_t slot =
-        (old & ~kCntMask) == cnt_epoch ? (uint32_t)(old & kCntMask) : 0xffffffffu;
-    if (slot >= (uint32_t)a.topk)
-      overflow_row(a, r, cnt_epoch);
-    else
-      a.inv[(long long)t * a.topk + slot] = (int32_t)r;
-  }
   __device__ __forceinline__ void claim(const KArgs& a, int rows_dev) {
     if (row >= rows_dev) row = -1;
     if (row >= 0 && !valid(a, tok)) row = -1;
@@ -341,12 +330,15 @@ struct RowShare {
       const long long r = (long long)blockIdx.x * per + i;
       if (r >= rows_dev) break;
       const int t = a.token_ids[r];
-      if (valid(a, t)) place(a, (int)r, t, take(a, t));
+      if (!valid(a, t)) continue;
+      RowPlace p;
+      p.take(a, t, cnt_epoch);
+      p.place(a, (int)r, t, cnt_epoch);
     }
-    if (row >= 0) slot_word = take(a, tok);
+    if (row >= 0) mine.take(a, tok, cnt_epoch);
   }
   __device__ __forceinline__ void finish(const KArgs& a) {
-    if (row >= 0) place(a, row, tok, slot_word);
+    if (row >= 0) mine.place(a, row, tok, cnt_epoch);
   }
   // the up-projection needs no inverse map
   __device__ __forceinline__ void load(const G1Args&) {}
@@ -908,6 +900,23 @@ mixed_gemm_kernel(Args a) {
 // completed epoch ends the launch pair (only the first launch reads it).
 constexpr int kSmallCombineWaves = 4;
 
+// Adds acc, this lane's columns 4 lane .. 4 lane + 3 of the 256 at o (of which
+// `cols` exist), each atomic on 64 neighbouring columns (on every fourth column
+// it touches four times the lines).
+__device__ __forceinline__ void add_block(float* o, int cols, const float (&acc)[4]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    int v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      v[e] = __builtin_amdgcn_ds_bpermute(4 * (16 * i + (lane >> 2)), __float_as_int(acc[e]));
+    const int even = lane & 1 ? v[1] : v[0], odd = lane & 1 ? v[3] : v[2];
+    const int c = 64 * i + lane;
+    if (c < cols) atomic_add_f32(o + c, __int_as_float(lane & 2 ? odd : even));
+  }
+}
+
 // Rows j0 .. j0+U-1 of a token (its sorted rows in lanes of rs, gates in gs)
 // at CB column blocks: all loads first, then the sums in ascending order.
 template <int U, int CB, bool kNtLoad>
@@ -931,7 +940,7 @@ __device__ __forceinline__ void small_gather(const uint16_t* y, int ypitch, int 
   }
 }
 
-template <int CB, bool kNtLoad>
+template <int CB, bool kNtLoad, bool kScatter>
 __device__ __forceinline__ void small_combine_unit(const KArgs& a, u64 epoch, long long unit,
                                                    int cbs) {
   const int lane = threadIdx.x & 63;
@@ -967,30 +976,73 @@ __device__ __forceinline__ void small_combine_unit(const KArgs& a, u64 epoch, lo
   if (n - j >= 4) small_gather<4, CB, kNtLoad>(a.Y, a.ypitch, j, rs, gs, col, acc), j += 4;
   if (n - j >= 2) small_gather<2, CB, kNtLoad>(a.Y, a.ypitch, j, rs, gs, col, acc), j += 2;
   if (n - j >= 1) small_gather<1, CB, kNtLoad>(a.Y, a.ypitch, j, rs, gs, col, acc);
-  if (a.mode == 1 && __builtin_amdgcn_readfirstlane(have) > (uint32_t)K) {
-    // a token with more than topk rows: the others are somewhere in the list
-    const long long slots = (long long)a.T * K;
-    const u64 listed = epoch_count(*a.over_cnt, cnt_epoch);
-    const int m = (int)(listed < (u64)slots ? listed : (u64)slots);
-    for (int i0 = 0; i0 < m; i0 += 64) {
-      const int row = i0 + lane < m ? a.inv[slots + i0 + lane] : -1;
-      u64 mine = __ballot(row >= 0 && a.token_ids[row < 0 ? 0 : row] == t);
-      const int gate = row >= 0 ? __float_as_int(a.gate_w[row]) : 0;
-      for (; mine; mine &= mine - 1)
-        small_gather<1, CB, kNtLoad>(a.Y, a.ypitch, (int)__builtin_ctzll(mine), row, gate, col, acc);
-    }
-  }
+  // (mode 1, a token with more than topk rows: the first launch zeroed its
+  // output, and small_add_listed adds the others)
+  const bool add = kScatter && __builtin_amdgcn_readfirstlane(have) > (uint32_t)K;
 #pragma unroll
-  for (int b = 0; b < CB; ++b)
-    if (c0 + 256 * b < a.H)
-      __builtin_nontemporal_store(f32x4{acc[b][0], acc[b][1], acc[b][2], acc[b][3]},
-                                  (f32x4*)(a.out + (size_t)t * a.H + c0 + 256 * b));
+  for (int b = 0; b < CB; ++b) {
+    float* o = a.out + (size_t)t * a.H + c0 + 256 * b;
+    if (add)
+      add_block(o - 4 * lane, a.H - (c0 - 4 * lane + 256 * b), acc[b]);
+    else if (c0 + 256 * b < a.H)
+      __builtin_nontemporal_store(f32x4{acc[b][0], acc[b][1], acc[b][2], acc[b][3]}, (f32x4*)o);
+  }
 }
 
+// Mode 1: the `listed` rows past their token's topk, eight at a time, spread over
+// every wave of the launch; neighbours of one token are summed before they are
+// added.  (One wave per token and column block for its part of the list, a load
+// at a time, took 13.2 ms where half of T = 8192, top-8, H = 1024 rows are one
+// token's; now 0.23.)
 template <int CB, bool kNtLoad>
+__device__ __forceinline__ void small_add_listed(const KArgs& a, int listed, int cbs) {
+  constexpr int U = 8;
+  const int lane = threadIdx.x & 63;
+  const int32_t* list = a.inv + (size_t)a.T * a.topk;
+  const long long groups = (listed + U - 1) / U;
+  for (long long k = (long long)blockIdx.x * kSmallCombineWaves +
+                     __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+       k < groups * cbs; k += (long long)gridDim.x * kSmallCombineWaves) {
+    const long long group = k / cbs;
+    const int c0 = (int)(k - group * cbs) * 256 * CB + 4 * lane;
+    const int n = min(U, (int)(listed - group * U));
+    const int r = list[group * U + min(lane, n - 1)];
+    const int t = a.token_ids[r], g = __float_as_int(a.gate_w[r]);
+    u32x2 v[U][CB];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const uint16_t* yr = a.Y + (size_t)__builtin_amdgcn_readlane(r, q) * a.ypitch;
+#pragma unroll
+      for (int b = 0; b < CB; ++b) {
+        const u32x2* p = (const u32x2*)(yr + (c0 + 256 * b < a.H ? c0 + 256 * b : 0));
+        v[q][b] = kNtLoad ? __builtin_nontemporal_load(p) : *p;
+      }
+    }
+    float acc[CB][4] = {};
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      if (q >= n) break;
+      const int tq = __builtin_amdgcn_readlane(t, q);
+#pragma unroll
+      for (int b = 0; b < CB; ++b) fma4(acc[b], __int_as_float(__builtin_amdgcn_readlane(g, q)), v[q][b]);
+      if (q + 1 < n && __builtin_amdgcn_readlane(t, q + 1 < U ? q + 1 : q) == tq) continue;
+#pragma unroll
+      for (int b = 0; b < CB; ++b) {
+        const int cb = c0 - 4 * lane + 256 * b;
+        add_block(a.out + (size_t)tq * a.H + cb, a.H - cb, acc[b]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[b][i] = 0.f;
+      }
+    }
+  }
+}
+
+// kScatter: mode 1
+template <int CB, bool kNtLoad, bool kScatter>
 __global__ void __launch_bounds__(kSmallCombineWaves * 64) small_combine_kernel(KArgs a) {
   const u64 epoch =
       __hip_atomic_load(a.map_epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const u64 over = kScatter ? __hip_atomic_load(a.over_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
   if (blockIdx.x == 0 && threadIdx.x == 0)
     __hip_atomic_store(a.epoch_word, (uint32_t)(epoch + 1) == 0 ? epoch + 1 : epoch,
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -999,5 +1051,11 @@ __global__ void __launch_bounds__(kSmallCombineWaves * 64) small_combine_kernel(
   for (long long unit = (long long)blockIdx.x * kSmallCombineWaves +
                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
        unit < units; unit += (long long)gridDim.x * kSmallCombineWaves)
-    small_combine_unit<CB, kNtLoad>(a, epoch, unit, cbs);
+    small_combine_unit<CB, kNtLoad, kScatter>(a, epoch, unit, cbs);
+  if constexpr (kScatter) {
+    const u64 cnt_epoch = (epoch & ((1ull << (64 - kCntBits)) - 1)) << kCntBits;
+    const long long slots = (long long)a.T * a.topk, n = epoch_count(over, cnt_epoch);
+    const int listed = __builtin_amdgcn_readfirstlane((int)(n < slots ? n : slots));
+    if (listed > 0) small_add_listed<CB, kNtLoad>(a, listed, cbs);
+  }
 }

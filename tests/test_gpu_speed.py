@@ -61,3 +61,29 @@ def test_many_experts(gpu_lib, E, H, I, rows):
     persistent, now = _median_us(call, 0, True), _median_us(call, 0, False)
     print(f"E={E} H={H} I={I} rows={rows}: persistent {persistent:.1f} us, two launches {now:.1f} us", flush=True)
     assert now <= 1.25 * persistent
+
+
+@pytest.mark.parametrize("name", ["one", "few", "half", "late"])
+def test_rows_past_topk(gpu_lib, name):
+    """The atomic scatter where tokens have more than topk rows: half of all
+    rows are one token's or 64 tokens', every second token has twice topk, and
+    one token's rows come at the end of every expert."""
+    def token_of(rng, n, T, topk):
+        tid = _spread(rng, n, T, topk)
+        if name == "one":
+            tid[rng.permutation(n)[:n // 2]] = 5
+        elif name == "few":
+            idx = rng.permutation(n)[:n // 2]
+            tid[idx] = rng.integers(0, 64, n // 2)
+        elif name == "half":
+            tid &= ~1
+        else:
+            tid[n // 16 * np.arange(1, 17)[:, None] - np.arange(1, 200)] = T - 1
+        return tid
+    call = _calls(16, 1024, 256, 4096, 8, token_of)
+    persistent, now = _median_us(call, 1, True), _median_us(call, 1, False)
+    print(f"{name}: persistent {persistent:.1f} us, two launches {now:.1f} us", flush=True)
+    assert now <= 1.25 * persistent
+    want, got = call(1, True).clone(), call(1, False)
+    # fp32 sums of up to 32768 terms of about unit size in other orders
+    assert (got - want).norm() <= 1e-5 * want.norm()
