@@ -315,12 +315,12 @@ int moe_gemm2_workspace_init(void* workspace, size_t workspace_bytes, void* stre
  *                   combine's (traced calls, and calls with the debugging
  *                   variables below set: one launch whose workgroups compute
  *                   their tiles and then take consumer tasks);
- *                   -1: the value returned is chosen by moe_select_partition with
- *                   moe_gemm2_launch_params(device, 0, wl), unless the
- *                   environment sets
- *                   MOE_GEMM2_SELECTOR=0, which restores a fixed C = 8; the
- *                   call runs as with 0 (a traced or debugged call, and the
- *                   atomic scatter, with the C returned)
+ *                   -1: the call runs as with 0, and the value returned is the
+ *                   C that moe_select_partition chooses for the one launch
+ *                   with moe_gemm2_launch_params(device, 0, wl); traced calls,
+ *                   and calls with the debugging variables below set, run
+ *                   with that C.  With MOE_GEMM2_SELECTOR=0 in the
+ *                   environment the call runs with a fixed C = 8
  *   workspace       device memory of at least moe_gemm2_workspace_size(wl)
  *                   bytes, 256-byte aligned, zeroed once by
  *                   moe_gemm2_workspace_init; calls that may overlap in

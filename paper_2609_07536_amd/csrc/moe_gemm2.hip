@@ -2569,10 +2569,12 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
   if (st != MOE_OK) return st;
 
   int C = num_consumers;
+  bool dedicated = C > 0;   // dedicated consumers asked for
   if (C < 0) {
     const char* sel = std::getenv("MOE_GEMM2_SELECTOR");
     if (sel && sel[0] == '0') {
       C = kDefaultFixedC;
+      dedicated = true;
     } else {
       moe_select_params_t p;
       fill_params(d, mode, wl->topk, mode == 2 ? band_tasks(wl).comm_tm : L.comm_tm, &p);
@@ -2692,7 +2694,7 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
   // (Mode 1: the same additions without atomics, while its overflow list holds
   // every row; its 16.8 M fp32 atomics at T = 2048, H = 1024, top-8 took about
   // 70 us of 107, the two launches take 30.)
-  if (!trace && num_consumers <= 0 && !wait_env &&
+  if (!trace && !dedicated && !wait_env &&
       (mode != 1 || (L.rows <= (long long)wl->T * wl->topk && L.rows < (long long)kCntMask))) {
     a.nsplit = wl->H;
     a.ysplit = round_up_line(wl->H);   // one segment; fits the column-split layout

@@ -93,3 +93,23 @@ for E, H, I, T, k in {shapes}:
     result.append([c[0] for c in launches() if "fill_zero" not in c[0]][0])
 ''')
     assert [g.split("_gemm_kernel")[0] for g in got] == [s[5] for s in ROUTES[op]], got
+
+
+def test_fixed_partition_by_environment(recorder):
+    """MOE_GEMM2_SELECTOR=0: a call that leaves the choice to the library runs
+    with eight dedicated consumers, in every mode; explicit counts win."""
+    got = launch_recorder.run(recorder, '''
+result = []
+for op in ("combine", "noalloc", "layer"):
+    for C in (-1, 0, 5):
+        for mode in ((0, 1, 2) if op != "layer" else (0,)):
+            used = call(op, T=300, H=512, I=64, E=8, topk=2, C=C, mode=mode)
+            last = launches()[-1]
+            result.append([C, used, last[0], last[1]])
+''', MOE_GEMM2_SELECTOR="0")
+    for C, used, kernel, grid in got:
+        assert used == (8 if C < 0 else C)
+        if C == 0:
+            assert "small_combine" in kernel
+        else:   # 256 CUs, one workgroup each
+            assert "moe_gemm2_fused" in kernel and grid == 256
