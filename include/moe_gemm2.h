@@ -350,8 +350,10 @@ int moe_gemm2_workspace_init(void* workspace, size_t workspace_bytes, void* stre
  * workgroups' tiles only once its whole grid has started, and dedicated
  * consumers (C >= 1) wait only on compute workgroups, which never wait; so
  * concurrent launches drain as long as their dedicated consumers together
- * leave a CU free.  Every wait is bounded (MOE_GEMM2_SPIN_LIMIT polls, then
- * MOE_ERR_TIMEOUT).  Debugging aid: MOE_GEMM2_DEBUG_PUBLISH_DELAY="m:t"
+ * leave a CU free.  Every wait is bounded (MOE_GEMM2_SPIN_LIMIT polls, 4000000
+ * by default, then MOE_ERR_TIMEOUT).  Debugging aids, which make also the calls
+ * without dedicated consumers and without a trace run as the persistent kernel:
+ * a lower MOE_GEMM2_SPIN_LIMIT, and MOE_GEMM2_DEBUG_PUBLISH_DELAY="m:t", which
  * makes the compute workgroups whose index is a multiple of m hold each
  * split publish back by t ticks of the 100 MHz clock (t <= 10^6).
  * Returns the number of consumer workgroups asked for or chosen (>= 0) or a

@@ -2125,6 +2125,7 @@ constexpr int64_t kRhoBandsDen = 100;
 constexpr int64_t kSplitCostBandsNum = 43;
 constexpr int64_t kSplitCostBandsDen = 100;
 constexpr int kDefaultFixedC = 8;
+constexpr long long kSpinLimit = 4000000;   // polls of one wait
 // C_max (eq:c-domain) from the kernel's saturation characterization: with
 // T = 16384, H = 2048, I = 704, E = 32, top-6, uniform routing, L = 2, the
 // launch takes 454 / 447 / 445 / 454 / 475 us at C = 64 / 72 / 80 / 96 /
@@ -2617,13 +2618,13 @@ int launch(const void* x_perm, const void* w2, const int32_t* expert_offsets,
   a.trace = reinterpret_cast<u64*>(trace);
   a.rows = L.rows;
   a.max_tiles = L.max_tiles;
-  a.spin_limit = 4000000;
+  a.spin_limit = kSpinLimit;
   bool wait_env = false;   // a debugging aid of the persistent kernel's waits is set
   if (const char* s = std::getenv("MOE_GEMM2_SPIN_LIMIT")) {
     long long v = std::atoll(s);
     if (v > 0) {
       a.spin_limit = v;
-      wait_env = true;
+      wait_env = v < kSpinLimit;   // (a longer wait is no aid to a call that never waits)
     }
   }
   a.T = wl->T;

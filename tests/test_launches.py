@@ -113,3 +113,16 @@ for op in ("combine", "noalloc", "layer"):
             assert "small_combine" in kernel
         else:   # 256 CUs, one workgroup each
             assert "moe_gemm2_fused" in kernel and grid == 256
+
+
+@pytest.mark.parametrize("limit,persistent", [("1", True), ("3999999", True), ("4000000", False),
+                                              ("100000000", False)])
+def test_wait_limit_by_environment(recorder, limit, persistent):
+    """MOE_GEMM2_SPIN_LIMIT bounds the persistent kernel's waits: a limit below
+    the built-in one makes the calls without dedicated consumers take it too; one
+    that is not leaves them to the launches that never wait."""
+    got = launch_recorder.run(recorder, '''
+assert call("combine", T=300, H=512, I=64, E=8, topk=2, C=0) == 0
+result = launches()[-1][0]
+''', MOE_GEMM2_SPIN_LIMIT=limit)
+    assert ("moe_gemm2_fused" in got) == persistent, got
