@@ -605,6 +605,11 @@ __device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) all += __shfl_xor(all, d);
   all = __builtin_amdgcn_readfirstlane(all);
+  // Offsets that decrease (they are flagged) can give every expert all rows.  The
+  // stage then has no tiles, as in the persistent kernel (the up-projection, as
+  // before, computes them, E times the rows at most).
+  if (!RowGather<Args>::on && all > (int)((a.rows + kBM - 1) / kBM) + a.E)
+    return {kBM - 1, false, 0, 0, 0, 0, 0, 0};
   // one round of full tiles holds everything (nothing to weigh: 3 us less)
   const int whole = (N + kBN - 1) / kBN;
   if (all <= small_div(P, whole)) return {kBM - 1, false, whole, all * whole, 0, 0, 0, 0};

@@ -222,3 +222,38 @@ def test_several_smaller_tiles_per_workgroup(gpu_lib, name):
         got = B.gemm1_swiglu(hidden, packed, off, tid, k, rows)
         # (the bound of test_up_projection_tiles)
         assert (got.float() - ref).abs().le(2 ** -8 * ref.abs() + 2e-4).all(), i
+
+
+def test_overlapping_expert_ranges_have_no_tiles(gpu_lib):
+    """Decreasing offsets that give half of the experts all rows make a large
+    batch's tiles many times those of the workload: the launch flags them and
+    computes none of them (the workspace's Y keeps what it held); the next call
+    on the workspace is right."""
+    import torch
+
+    from paper_2609_07536_amd import binding as B
+    T, H, I, E, k = 4096, 2048, 64, 32, 8
+    rows, gen = T * k, torch.Generator(device="cuda").manual_seed(6)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device="cuda").bfloat16()
+
+    x, w2, gate = normal(rows, I), normal(E, I, H), torch.rand(rows, generator=gen, device="cuda")
+    tid = torch.arange(T, device="cuda", dtype=torch.int32).repeat(k)
+    off = torch.arange(E + 1, device="cuda", dtype=torch.int32) * (rows // E)
+    bad = torch.tensor([0, rows] * (E // 2) + [rows], device="cuda", dtype=torch.int32)
+    wl, _ = B.make_workload(T, H, I, E, k, 1, rows=rows)
+    ws = B.Workspace(B.workspace_size(wl))
+    out = torch.empty((T, H), device="cuda")
+
+    def stage(offsets, C):
+        B.combine(x, w2, offsets, tid, gate, T=T, topk=k, num_consumers=C, out=out, workspace=ws)
+        return out.clone()
+
+    ref = stage(off, 3)
+    y = ws.tensor[ws.nbytes // 2:ws.nbytes - 256]   # Y is the workspace's last and largest part
+    y.fill_(0x11)
+    stage(bad, 0)
+    assert ws.status(clear=True) == B.MOE_ERR_BAD_ROUTING
+    assert bool((y == 0x11).all())
+    assert torch.equal(stage(off, 0), ref) and ws.status() == 0
