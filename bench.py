@@ -161,7 +161,8 @@ def settle(dw, C, torch, ms=60.0):
 
 
 def breakdown(dw, C, mode=None, reps=5):
-    """GEMM portion and combine from traced launches: the launch with the
+    """GEMM portion and combine from traced launches (of the persistent kernel,
+    which a trace always takes): the launch with the
     median GEMM span out of `reps` (each after a short pause, so that one
     launch's clock state does not decide the figure)."""
     w = dw.w
@@ -232,6 +233,20 @@ def launch_cfg(dw, c):
     if isinstance(c, tuple):
         return dw.run(c[0], mode=c[1], splits=c[2] if len(c) > 2 else None)
     return dw.run(c)
+
+
+def launch_persistent(dw, c):
+    """launch_cfg by the persistent kernel, which the selector models, also with
+    C = 0 (a wait limit just below the default makes such a call take it);
+    c = -1: the library's own call, without dedicated consumers."""
+    C = c[0] if isinstance(c, tuple) else c
+    if C != 0:
+        return launch_cfg(dw, c)
+    os.environ["MOE_GEMM2_SPIN_LIMIT"] = "3999999"
+    try:
+        return launch_cfg(dw, c)
+    finally:
+        del os.environ["MOE_GEMM2_SPIN_LIMIT"]
 
 
 def time_configs(launch, keys, samples, warmups, torch):
@@ -311,13 +326,15 @@ class SweepPoint:
 
 def run_sweep(B, torch, samples, warmups, repeats=2, c_max=64):
     """The selector sweep: the 12 workloads x C = 0..c_max (owner-write,
-    column splits, as the selector's launch uses), every C timed `samples`
-    times (ABBA) after `warmups` passes; the whole sweep is repeated
-    `repeats` times (independent passes, the second over the workloads in
-    reverse order).  Regret = (t(pick) - t(best)) / t(best) on medians, for
-    the library's candidate set 0..64 and for the paper's 1..64 (against
-    the best in 1..64).  Also the token-band consumer over a grid of (C, L)
-    with the selector's joint (C, L) pick."""
+    column splits, on the persistent kernel, which the selector partitions),
+    every C timed `samples` times (ABBA) after `warmups` passes; the whole
+    sweep is repeated `repeats` times (independent passes, the second over
+    the workloads in reverse order).  Regret = (t(pick) - t(best)) / t(best)
+    on medians, for the library's candidate set 0..64 and for the paper's
+    1..64 (against the best in 1..64).  Also the token-band consumer over a
+    grid of (C, L) with the selector's joint (C, L) pick, and the library's
+    own call (num_consumers = -1), which runs without dedicated consumers,
+    against the best of 0..64."""
     from workloads import sweep_workloads
     names = [n for n, _ in sweep_workloads()]
     points = []
@@ -335,13 +352,13 @@ def run_sweep(B, torch, samples, warmups, repeats=2, c_max=64):
             # the band pick among its grid neighbours (ordered by L, then C),
             # not at an end of the pass
             band_keys = sorted(set(band_grid) | {pt.pick_bands}, key=lambda k: (k[2], k[0]))
-            keys = Cs + band_keys
-            t = time_configs(lambda c: launch_cfg(pt.dw, c), keys, samples, warmups, torch)
+            keys = [-1] + Cs + band_keys
+            t = time_configs(lambda c: launch_persistent(pt.dw, c), keys, samples, warmups, torch)
             assert pt.dw.ws.status() == 0
             res[pt.name] = {k: median_ci(v) for k, v in t.items()}
         runs.append(res)
     rows = []
-    per_rep = {"regret": [], "paper": [], "estimate": [], "bands": []}
+    per_rep = {"regret": [], "paper": [], "estimate": [], "bands": [], "call": []}
     for pt in points:
         row = {"w": pt.name, "r_expert": round(pt.w.r_expert, 2)}
         for ri, res in enumerate(runs):
@@ -358,6 +375,8 @@ def run_sweep(B, torch, samples, warmups, repeats=2, c_max=64):
             per_rep["paper"].append((ri, rp))
             per_rep["estimate"].append((ri, re))
             per_rep["bands"].append((ri, rb))
+            rc = _regret(st, -1, best)
+            per_rep["call"].append((ri, rc))
             f = lambda k: [round(x, 1) for x in st[k]]   # noqa: E731
             row[f"s{ri + 1}"] = {
                 "best": [best] + f(best), "pick": [pt.pick] + f(pt.pick), "regret": round(r, 4),
@@ -367,6 +386,7 @@ def run_sweep(B, torch, samples, warmups, repeats=2, c_max=64):
                 "bands_best": [best_b[0], best_b[2]] + f(best_b),
                 "bands_pick": [pt.pick_bands[0], pt.pick_bands[2]] + f(pt.pick_bands),
                 "regret_bands": round(rb, 4),
+                "call": f(-1), "call_over_best": round(1 + rc, 4),
                 "c0_vs_best_paper_set": round(st[0][0] / st[best_dom][0], 4)}
         rows.append(row)
 
@@ -382,7 +402,8 @@ def run_sweep(B, torch, samples, warmups, repeats=2, c_max=64):
     summary = {"workloads": len(rows), "samples_per_C": samples, "warmups": warmups,
                "sweeps": repeats, "C_range": [0, c_max],
                "regret": by_rep("regret"), "regret_paper_set": by_rep("paper"),
-               "regret_estimate": by_rep("estimate"), "regret_bands": by_rep("bands")}
+               "regret_estimate": by_rep("estimate"), "regret_bands": by_rep("bands"),
+               "call_against_best": by_rep("call")}
     detail = {"per_workload": rows,
               "us_by_C_sweep1": {pt.name: {str(c): round(runs[0][pt.name][c][0], 1) for c in Cs}
                                  for pt in points},
@@ -791,6 +812,8 @@ def main():
         "selector_us_net_of_ctypes": round(max(sel_us - nop_us, 0.0), 3),
         "gemm_portion": {k: round(v, 3) for k, v in gemm_portion.items()},
         "combine": {k: round(v, 3) for k, v in combine.items()} if combine else None,
+        # (the timed call's own launches write no trace)
+        "gemm_portion_and_combine_of": "a traced launch of the persistent kernel at C = consumers",
         "scatter_mode": scatter,
         "layer": layer_res,
         "roofline": {"bound": "mfma", "achieved": round(achieved, 2),
