@@ -1,5 +1,8 @@
 """Helpers for the GPU tests: move a workload to the device and run the stage
 through the C ABI."""
+import contextlib
+import os
+
 import numpy as np
 import torch
 
@@ -13,6 +16,23 @@ def to_device(w, device="cuda"):
     tid = torch.from_numpy(w.token_ids.astype(np.int32)).to(device)
     g = torch.from_numpy(w.gate_w.astype(np.float32)).to(device)
     return x, w2, off, tid, g
+
+
+@contextlib.contextmanager
+def persistent(on=True):
+    """Calls without dedicated consumers (C = 0 or -1) made here run as the
+    persistent kernel too, with the role switch at C = 0: a wait limit just below
+    the default makes them (launches wait as long as ever)."""
+    old = os.environ.get("MOE_GEMM2_SPIN_LIMIT")
+    if on:
+        os.environ["MOE_GEMM2_SPIN_LIMIT"] = "3999999"
+    try:
+        yield
+    finally:
+        if on and old is None:
+            del os.environ["MOE_GEMM2_SPIN_LIMIT"]
+        elif on:
+            os.environ["MOE_GEMM2_SPIN_LIMIT"] = old
 
 
 def run(w, C=-1, dev=None, workspace=None, counts=True, splits=None, trace=None,

@@ -4,7 +4,8 @@ hold its rows, agent-coherent reads of Y, compute workgroups draining into
 consumers.  The owner-write sum order (ascending row per token) does not
 depend on the split or the partition, so the output must be bitwise the
 column-split owner-write output (mode 0) for every band count and C, and
-within the bar of the oracle.
+within the bar of the oracle.  (Without dedicated consumers a call runs as two
+launches without bands; C = 0 is run both ways here, see _run.)
 """
 import numpy as np
 import pytest
@@ -24,6 +25,19 @@ def _check(got, ref, what=""):
     assert np.isfinite(got).all()
     assert rl2 <= oc.REL_L2_TOL, (what, rl2)
     assert mab <= oc.MAX_ABS_TOL, (what, mab)
+
+
+def _run(w, C, **kw):
+    """The outputs of a call: with C = 0 the persistent kernel's role switch, then
+    the two launches."""
+    import gpu_util
+    outs = []
+    for role in ((True, False) if C == 0 else (False,)):
+        with gpu_util.persistent(role):
+            got, used, _ = gpu_util.run(w, C=C, **kw)
+        assert used == C
+        outs.append(got)
+    return outs
 
 
 def _base(name):
@@ -47,11 +61,10 @@ def test_bands_configs_bitwise(gpu_lib, name, L):
     w, ref, dev, ws, base = _base(name)
     for C in (0, 1, 16, 48):
         print(f"{name} bands L={L} C={C}", flush=True)
-        got, used, _ = gpu_util.run(w, C=C, dev=dev, workspace=ws, mode=2, splits=L)
-        assert used == C
-        if not np.array_equal(got.view(np.uint32), base.view(np.uint32)):
-            _check(got, ref, f"{name} bands L={L} C={C}")
-            raise AssertionError(f"{name} L={L} C={C}: not bitwise equal to mode 0")
+        for got in _run(w, C, dev=dev, workspace=ws, mode=2, splits=L):
+            if not np.array_equal(got.view(np.uint32), base.view(np.uint32)):
+                _check(got, ref, f"{name} bands L={L} C={C}")
+                raise AssertionError(f"{name} L={L} C={C}: not bitwise equal to mode 0")
 
 
 EDGE = [
@@ -79,8 +92,8 @@ def test_bands_edge_shapes(gpu_lib, case):
     base, _, _ = gpu_util.run(w, C=0, dev=dev)
     _check(base, ref, f"{name} mode 0")
     for C in (0, 1, 5):
-        got, used, _ = gpu_util.run(w, C=C, dev=dev, mode=2, splits=L)
-        assert np.array_equal(got.view(np.uint32), base.view(np.uint32)), (name, C)
+        for got in _run(w, C, dev=dev, mode=2, splits=L):
+            assert np.array_equal(got.view(np.uint32), base.view(np.uint32)), (name, C)
 
 
 def test_bands_unsorted_rows(gpu_lib):
@@ -100,8 +113,8 @@ def test_bands_unsorted_rows(gpu_lib):
     base, _, _ = gpu_util.run(w, C=0, dev=dev)
     _check(base, ref, "unsorted mode 0")
     for L, C in ((4, 0), (4, 8), (8, 3)):
-        got, used, _ = gpu_util.run(w, C=C, dev=dev, mode=2, splits=L)
-        assert np.array_equal(got.view(np.uint32), base.view(np.uint32)), (L, C)
+        for got in _run(w, C, dev=dev, mode=2, splits=L):
+            assert np.array_equal(got.view(np.uint32), base.view(np.uint32)), (L, C)
 
 
 def test_bands_dropped_slots_and_no_rows(gpu_lib):
@@ -119,9 +132,9 @@ def test_bands_dropped_slots_and_no_rows(gpu_lib):
     ref = oc.combine_reference(w.x_perm, w.w2, w.expert_offsets, w.token_ids, w.gate_w, w.T)
     empty = [t for t in range(T) if len(sel[t]) == 0]
     for L, C in ((1, 0), (3, 2), (6, 0)):
-        got, used, _ = gpu_util.run(w, C=C, mode=2, splits=L)
-        _check(got, ref, f"dropped bands L={L} C={C}")
-        assert np.all(got[empty] == 0)
+        for got in _run(w, C, mode=2, splits=L):
+            _check(got, ref, f"dropped bands L={L} C={C}")
+            assert np.all(got[empty] == 0)
     w0 = explicit(50, 256, 32, 4, [[] for _ in range(50)], [[] for _ in range(50)])
     w0.topk = 2
     w0.x_perm = np.zeros((1, 32), dtype=np.uint16)

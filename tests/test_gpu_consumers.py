@@ -30,8 +30,8 @@ def _check(got, ref, what=""):
 
 
 def _full(name):
-    """Workload, oracle output, device tensors, workspace and the C = 0
-    output (checked against the oracle once)."""
+    """Workload, oracle output, device tensors, workspace and the output of the
+    two launches without dedicated consumers (checked against the oracle once)."""
     if name not in _cache:
         import gpu_util
         w = sweep_workload(name) if name.startswith("sweep_") else config(name)
@@ -63,18 +63,20 @@ def test_dedicated_consumers_full_size_bitwise(gpu_lib, name, C):
         _check(got, ref, f"{name} C=64 vs oracle")
 
 
-@pytest.mark.parametrize("mode,C", [(0, 56), (0, 60), (2, 0), (2, 1), (2, 8), (1, 0)])
+@pytest.mark.parametrize("mode,C", [(0, 0), (0, 56), (0, 60), (2, 0), (2, 1), (2, 8), (1, 0)])
 def test_rotated_rounds_largest_sweep_shape(gpu_lib, mode, C):
     """T = 32768 has about 25 compute rounds, so workgroups whose P is a
     multiple of the n-tiles per m-tile take their tiles rotated by one more
     each round (C = 0, 56 and 60 with column splits, C = 0 and 8 with token
     bands; C = 1 with bands and C = 57 keep the plain order).  Owner-write
-    results stay bitwise equal to the oracle-checked C = 0 output; the atomic
-    scatter is checked against the oracle."""
+    results of the persistent kernel are bitwise equal to the oracle-checked
+    output of the two launches; the atomic scatter is checked against the
+    oracle."""
     import gpu_util
     w, ref, dev, ws, base = _full("sweep_T32768_uniform")
     print(f"T=32768 mode={mode} C={C}", flush=True)
-    got, used, _ = gpu_util.run(w, C=C, dev=dev, workspace=ws, mode=mode)
+    with gpu_util.persistent():
+        got, used, _ = gpu_util.run(w, C=C, dev=dev, workspace=ws, mode=mode)
     assert used == C
     if mode == 1:
         _check(got, ref, f"T=32768 scatter C={C}")
@@ -116,9 +118,10 @@ def test_delayed_publishes(gpu_lib, C):
 
 def test_thousand_launches_one_workspace(gpu_lib):
     """1000 launches back to back on one workspace, cycling C over
-    {0, 1, 8, 64} and both consumer modes: every owner-write output is
-    bitwise the first one, every scatter output within the bar of it
-    (compared on the device); stops at the first mismatch or error."""
+    {0, 1, 8, 64}, C = 0 as two launches and as the role switch, and both
+    consumer modes: every owner-write output is bitwise the first one, every
+    scatter output within the bar of it (compared on the device); stops at the
+    first mismatch or error."""
     import torch
 
     import gpu_util
@@ -135,12 +138,14 @@ def test_thousand_launches_one_workspace(gpu_lib):
     first = out.clone()
     _check(first.cpu().numpy(), ref, "first launch")
     ref_max = float(first.abs().max())
-    plan = [(C, mode) for mode in (0, 1) for C in (0, 1, 8, 64)]
+    plan = [(C, mode, role) for mode in (0, 1)
+            for C, role in ((0, False), (1, False), (0, True), (8, False), (64, False))]
     for i in range(1000):
-        C, mode = plan[i % len(plan)]
+        C, mode, role = plan[i % len(plan)]
         out.fill_(float("nan"))
-        B.combine(x, w2, off, tid, g, T=w.T, splits=w.L, topk=w.topk, counts=w.counts,
-                  num_consumers=C, out=out, workspace=ws, mode=mode)
+        with gpu_util.persistent(role):
+            B.combine(x, w2, off, tid, g, T=w.T, splits=w.L, topk=w.topk, counts=w.counts,
+                      num_consumers=C, out=out, workspace=ws, mode=mode)
         if mode == 0:
             ok = bool(torch.equal(out, first))
         else:
@@ -172,10 +177,11 @@ def test_workspace_reused_across_layouts(gpu_lib):
             for w in shapes]
     for rnd in range(2):
         for i, (w, ref) in enumerate(zip(shapes, refs)):
-            for C, mode in ((0, 0), (5, 0), (0, 1)):
-                print(f"relayout round {rnd} shape {i} C={C} mode={mode}", flush=True)
-                got, used, ws = gpu_util.run(w, C=C, workspace=ws, mode=mode)
-                _check(got, ref, f"shape {i} C={C} mode={mode}")
+            for C, mode, role in ((0, 0, False), (5, 0, False), (0, 0, True), (0, 1, False), (0, 1, True)):
+                print(f"relayout round {rnd} shape {i} C={C} mode={mode} role={role}", flush=True)
+                with gpu_util.persistent(role):
+                    got, used, ws = gpu_util.run(w, C=C, workspace=ws, mode=mode)
+                _check(got, ref, f"shape {i} C={C} mode={mode} role={role}")
 
 
 def test_fresh_workspaces_read_published_y_only(gpu_lib):
@@ -186,8 +192,9 @@ def test_fresh_workspaces_read_published_y_only(gpu_lib):
     workspace's zeros instead of the previous launch's identical Y, so the
     output differs.  Shapes whose tiles are a single reduction stage (I = 40)
     or have a partial width (H = 200) publish soonest after their stores;
-    every launch must be bitwise equal to the first (mode 0 and token bands,
-    dedicated consumers and the role switch)."""
+    every launch must be bitwise equal to the two launches' output, whose kernel
+    boundary is the only dependency (mode 0 and token bands, dedicated consumers
+    and the role switch; and the two launches on fresh workspaces)."""
     import gpu_util
     cases = [
         (custom(T=257, H=264, I=40, E=5, topk=2, L=1, routing=("uniform",), seed=13),
@@ -204,5 +211,9 @@ def test_fresh_workspaces_read_published_y_only(gpu_lib):
             print(f"fresh workspaces T={w.T} H={w.H} I={w.I} C={C} mode={mode} L={L} x{reps}",
                   flush=True)
             for it in range(reps):
-                got, _, _ = gpu_util.run(w, C=C, dev=dev, mode=mode, splits=L)
+                with gpu_util.persistent():
+                    got, _, _ = gpu_util.run(w, C=C, dev=dev, mode=mode, splits=L)
                 assert np.array_equal(got.view(np.uint32), base.view(np.uint32)), (C, mode, L, it)
+                if C == 0:
+                    got, _, _ = gpu_util.run(w, C=C, dev=dev, mode=mode, splits=L)
+                    assert np.array_equal(got.view(np.uint32), base.view(np.uint32)), (mode, L, it)

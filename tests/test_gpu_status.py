@@ -148,12 +148,13 @@ def test_watchdog_expires_and_next_launch_is_clean(gpu_lib):
 
 
 def test_two_streams_at_once(gpu_lib):
-    """Two launches in flight together on two streams with two workspaces
-    (each with its own consumers or the role switch) both come out right.
-    The launches share no device state, and a grid that is not fully
+    """Two calls in flight together on two streams with two workspaces (each
+    with its own consumers, the role switch or two launches) both come out
+    right.  The calls share no device state, and a grid that is not fully
     resident still drains: compute workgroups never wait while they hold
-    tiles, and with C = 0 a workgroup serves (and waits for) consumer tasks
-    only once every workgroup of its grid has started."""
+    tiles, with the role switch a workgroup serves (and waits for) consumer
+    tasks only once every workgroup of its grid has started, and the two
+    launches never wait."""
     import torch
 
     import gpu_util
@@ -170,11 +171,14 @@ def test_two_streams_at_once(gpu_lib):
         wss.append(B.Workspace(B.workspace_size(wl)))
     torch.cuda.synchronize()
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]   # default priority
-    for Cs in ((0, 4), (8, 0), (3, 3)):
-        for w, d, o, ws, st, C in zip((wa, wb), devs, outs, wss, streams, Cs):
-            x, w2, off, tid, g = d
-            B.combine(x, w2, off, tid, g, T=w.T, splits=w.L, topk=w.topk, counts=w.counts,
-                      num_consumers=C, out=o, workspace=ws, stream=st)
+    for Cs, role in (((0, 4), True), ((0, 4), False), ((8, 0), True), ((8, 0), False),
+                     ((0, 0), True), ((0, 0), False), ((3, 3), False)):
+        print(f"two streams C={Cs} role switch={role}", flush=True)
+        with gpu_util.persistent(role):
+            for w, d, o, ws, st, C in zip((wa, wb), devs, outs, wss, streams, Cs):
+                x, w2, off, tid, g = d
+                B.combine(x, w2, off, tid, g, T=w.T, splits=w.L, topk=w.topk, counts=w.counts,
+                          num_consumers=C, out=o, workspace=ws, stream=st)
         torch.cuda.synchronize()
         for w, o, ws, ref, C in zip((wa, wb), outs, wss, refs, Cs):
             assert ws.status() == 0
@@ -227,10 +231,13 @@ def test_scatter_traced_records_every_tile_task(gpu_lib):
 
 
 
-def test_graph_capture_replays(gpu_lib):
-    """The stage captured in a HIP graph (host counts absent, so the selector
-    uses the even-load estimate and needs nothing from the device) and
-    replayed: every replay equals the eager launch bitwise, with eager
+@pytest.mark.parametrize("C,role", [(-1, False), (0, True), (8, False)],
+                         ids=["two_launches", "role_switch", "consumers"])
+def test_graph_capture_replays(gpu_lib, C, role):
+    """The stage captured in a HIP graph, as two launches (host counts absent, so
+    the selector uses the even-load estimate and needs nothing from the device),
+    as the persistent kernel with the role switch and with dedicated consumers,
+    and replayed: every replay equals the eager launch bitwise, with eager
     launches and synchronisations between replays.  Each launch's epoch
     comes from the workspace, so replays of the same captured arguments
     never see the previous replay's flags."""
@@ -243,22 +250,26 @@ def test_graph_capture_replays(gpu_lib):
     x, w2, off, tid, g = gpu_util.to_device(w)
     wl, _ = B.make_workload(w.T, w.H, w.I, w.E, w.topk, w.L)
     B.default_params(0)                       # device facts cached before the capture
+
+    def call(mode, ws, out, stream):
+        with gpu_util.persistent(role):
+            B.combine(x, w2, off, tid, g, T=w.T, splits=w.L, topk=w.topk, num_consumers=C, out=out,
+                      workspace=ws, stream=stream, mode=mode)
+
     for mode in (0, 1):
         ws = B.Workspace(B.workspace_size(wl))
         out = torch.empty((w.T, w.H), dtype=torch.float32, device="cuda")
         side = torch.cuda.Stream()
         side.wait_stream(torch.cuda.current_stream())
         with torch.cuda.stream(side):         # warm-up launch on the capture stream
-            B.combine(x, w2, off, tid, g, T=w.T, splits=w.L, topk=w.topk, out=out,
-                      workspace=ws, stream=side, mode=mode)
+            call(mode, ws, out, side)
         torch.cuda.current_stream().wait_stream(side)
         torch.cuda.synchronize()
         eager = out.cpu().numpy().copy()
         _check(eager, ref, f"graph eager mode={mode}")
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, stream=side):
-            B.combine(x, w2, off, tid, g, T=w.T, splits=w.L, topk=w.topk, out=out,
-                      workspace=ws, stream=side, mode=mode)
+            call(mode, ws, out, side)
         for i in range(4):
             out.fill_(float("nan"))
             graph.replay()
@@ -269,7 +280,6 @@ def test_graph_capture_replays(gpu_lib):
             else:
                 _check(got, ref, f"graph replay {i} scatter")
             # an eager launch on the same workspace between replays
-            B.combine(x, w2, off, tid, g, T=w.T, splits=w.L, topk=w.topk, out=out,
-                      workspace=ws, mode=mode)
+            call(mode, ws, out, None)
             torch.cuda.synchronize()
             assert ws.status() == 0
