@@ -34,15 +34,15 @@ CASES = {
     # with 128 x 128 ones for a last column block that is at most half full
     "wide": lambda: custom(T=515, H=8192, I=72, E=8, topk=2, L=2, seed=7),
     "wide_edges": lambda: _edge_counts([127, 128, 129, 255, 256, 257, 70], 300, 8456, 40, 24),
-    "half_block": lambda: custom(T=515, H=4168, I=64, E=8, topk=2, L=1, seed=25),
+    "half_block": lambda: custom(T=520, H=4168, I=64, E=8, topk=2, L=1, seed=25),
     # more experts than a wave has lanes, most of them without rows
     "experts_200": lambda: custom(T=40, H=512, I=64, E=200, topk=3, L=1, seed=8),
     # expert row counts at the edges of the 64- and 128-row tiles, empty experts
     "edges_64": lambda: _edge_counts([63, 0, 64, 65, 1, 0, 33], 130, 520, 136, 9),
-    "edges_128": lambda: _edge_counts([127, 128, 0, 129, 255, 256, 257, 1], 300, 4104, 24, 10),
-    # more than two 256 x 256 tiles per CU: full tiles, and 256 x 128 edges and
-    # 128 x 256 bottoms as the plan of the launch has it; rows past a full
-    # tile at the plan's limits (64, 128 and 192 of them), empty experts
+    "edges_128": lambda: _edge_counts([127, 128, 0, 129, 255, 256, 257, 1], 300, 2056, 24, 10),
+    # more than two 256 x 256 tiles per CU: full tiles, with 256 x 128 edges and
+    # 128 x 256 bottoms if the launch's plan has them (each plan: LARGE below);
+    # rows past a full tile at the plan's limits (64, 128 and 192), empty experts
     "full_and_rest": lambda: _edge_counts([300] * 14, 400, 8320, 264, 21),
     "full_edges": lambda: _edge_counts([256, 257, 0, 255, 192, 193, 320, 321, 384, 385, 448, 449,
                                         64, 63, 1], 500, 8328, 40, 22),
@@ -50,6 +50,15 @@ CASES = {
                                              72, 23),
     "full_rounds": lambda: _edge_counts([2000, 2060, 1, 1990, 2048], 2100, 4104, 24, 24),
     "topk_64": lambda: custom(T=70, H=256, I=32, E=64, topk=64, L=1, seed=11),
+}
+
+
+# the tiles each of them is meant to run as (checked on the CPU by test_launches.py)
+TILES = {
+    "one_token": "64x64", "k_tail": "64x64", "deep_ring": "64x128 deep", "many_tiles": "64x128",
+    "wide": "128x256", "wide_edges": "128x256", "half_block": "128x256", "experts_200": "64x128 deep",
+    "edges_64": "64x64", "edges_128": "128x128", "full_and_rest": "full", "full_edges": "full",
+    "full_100_experts": "full", "full_rounds": "full", "topk_64": "64x128 deep",
 }
 
 
@@ -130,13 +139,21 @@ UP = {
     "k_tail": (5, 264, 48, 40, 2),
     "deep_ring": (32, 520, 512, 64, 8),
     "many_tiles": (64, 264, 672, 128, 4),
+    "tiles_128": (8, 136, 2048, 515, 2),
+    "tiles_128_tail": (8, 136, 2064, 515, 2),
     "wide": (8, 136, 4096, 515, 2),
     "half_block": (8, 128, 4160, 515, 2),
+    "wide_edge": (14, 264, 2112, 1400, 3),
     "experts_200": (200, 256, 80, 60, 3),
-    # full tiles with smaller ones for the rest, with and without an edge
-    "full_edge": (14, 264, 2112, 1400, 3),
+    # full tiles (with smaller ones for the rest: LARGE below)
     "full_no_edge": (10, 136, 1984, 2100, 4),
     "full_100_experts": (100, 64, 1072, 3000, 6),
+}
+UP_TILES = {
+    "one_token": "64x64", "odd": "64x64", "k_tail": "64x64", "deep_ring": "64x128 deep",
+    "many_tiles": "64x128", "tiles_128": "128x128", "tiles_128_tail": "128x128", "wide": "128x256",
+    "half_block": "128x256", "wide_edge": "128x256", "experts_200": "64x128 deep",
+    "full_no_edge": "full", "full_100_experts": "full",
 }
 
 
@@ -165,53 +182,99 @@ def test_up_projection_tiles(gpu_lib, name):
     assert (got.float() - ref).abs().le(2 ** -8 * ref.abs() + 2e-4).all()
 
 
-# E, H, I, rows of expert e: many more smaller tiles than CUs, so that a
-# workgroup takes several (by its index, or in fixed shares),
-# with and without a narrower last column block
-MANY = {
-    "bottoms": (300, 2048, 1040, lambda e: 30 + e % 31),
-    "edges": (700, 264, 512, lambda e: 1 + 5 * e % 90),
-    "both": (150, 1096, 1040, lambda e: 100 + 7 * e % 400),
-    "few_full": (270, 2304, 768, lambda e: 240 + e % 40 if e % 3 else 0),
+# Full tiles with smaller ones for the rest: E, columns, reduction, rows of
+# expert e, and what the stage's plan has: rows past a full tile that are one
+# themselves (255: all), and whether a narrow last column block has its own tiles.
+LARGE = {
+    "bottoms_192": (24, 2048, 1040, lambda e: 1100 + 37 * e % 60, 63, 0),
+    "bottoms_128": (60, 2048, 1040, lambda e: 600 + 37 * e % 60, 127, 0),
+    "whole": (60, 2048, 520, lambda e: 100 + 37 * e % 120, 255, 0),
+    "edge_bottoms_192": (16, 2120, 520, lambda e: 1100 + 37 * e % 60, 63, 1),
+    "edge_bottoms_128": (60, 1096, 1040, lambda e: 600 + 37 * e % 256, 127, 1),
+    "edge": (60, 2120, 520, lambda e: 100 + 37 * e % 60, 255, 1),
+    # many more smaller tiles than CUs: a workgroup takes several
+    "many_bottoms": (300, 2048, 1040, lambda e: 30 + e % 31, 63, 0),
+    "many_edges": (700, 264, 512, lambda e: 1 + 5 * e % 90, 255, 1),
+    "many_both": (150, 1096, 1040, lambda e: 100 + 7 * e % 400, None, 1),
+    "few_full": (270, 2304, 768, lambda e: 240 + e % 40 if e % 3 else 0, None, 0),
+}
+# the same of the up-projection, whose plan has other prices
+UP_LARGE = {
+    "bottoms_192": (24, 2048, 1040, lambda e: 300 + 37 * e % 256),
+    "bottoms_128": (60, 2048, 1040, lambda e: 600 + 37 * e % 60),
+    "whole": (40, 2048, 1040, lambda e: 100 + 37 * e % 256),
+    "edge_bottoms_192": (16, 2112, 1040, lambda e: 1100 + 37 * e % 60),
+    "edge_bottoms_128": (60, 1088, 1040, lambda e: 400 + 37 * e % 256),
+    "edge": (60, 2112, 1040, lambda e: 100 + 37 * e % 60),
+    "many_bottoms": (300, 2080, 2048, lambda e: 30 + e % 31),
+    "many_edges": (700, 320, 512, lambda e: 1 + 5 * e % 90),
 }
 
 
-@pytest.mark.parametrize("name", list(MANY))
-def test_several_smaller_tiles_per_workgroup(gpu_lib, name):
-    """The stage bitwise against the persistent kernel (three consumers), the
-    up-projection against fp32 torch, three calls each on one workspace."""
+def _routing(E, rows_of, k=4):
+    """Row counts, token count, offsets, tokens: every token has k rows at most."""
+    import torch
+    counts = np.array([rows_of(e) for e in range(E)])
+    rows = int(counts.sum())
+    T = -(-rows // k)
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    rng = np.random.default_rng(5)
+    tid = rng.permutation(np.repeat(np.arange(T), k)[:rows]).astype(np.int32)
+    return rows, T, torch.from_numpy(off).cuda(), torch.from_numpy(tid).cuda()
+
+
+def _left_plan(ws):
+    """What the stage's GEMM left in the workspace: pad, edge, edges, bottoms."""
+    at = ws.ptr - ws.tensor.data_ptr() + 352
+    w = ws.tensor[at:at + 24].cpu().numpy().view(np.uint64) & 0xffffffff
+    return int(w[0]) >> 1, int(w[0]) & 1, int(w[1]), int(w[2])
+
+
+@pytest.mark.parametrize("name", list(LARGE))
+def test_stage_full_tiles_with_smaller_ones(gpu_lib, name):
+    """Bitwise against the persistent kernel (three consumers), several calls on
+    one workspace; the plan is the one the case is for."""
     import torch
 
     from paper_2609_07536_amd import binding as B
-    E, H, I, rows_of = MANY[name]
-    counts = np.array([rows_of(e) for e in range(E)])
-    rows, k = int(counts.sum()), 4
-    T = -(-rows // k)
-    off = torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)).cuda()
-    rng = np.random.default_rng(5)
-    tid = torch.from_numpy(rng.permutation(np.repeat(np.arange(T), k)[:rows]).astype(np.int32)).cuda()
+    E, H, I, rows_of, pad, edge = LARGE[name]
+    rows, T, off, tid = _routing(E, rows_of)
     print(f"{name}: E={E} H={H} I={I} T={T} rows={rows}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(2)
-
-    def normal(*shape):
-        return torch.randn(shape, generator=gen, device="cuda").bfloat16()
-
-    x, w2, gate = normal(rows, I), normal(E, I, H), torch.rand(rows, generator=gen, device="cuda")
-    wl, _ = B.make_workload(T, H, I, E, k, 1, rows=rows)
+    x = torch.randn((rows, I), generator=gen, device="cuda").bfloat16()
+    w2 = torch.randn((E, I, H), generator=gen, device="cuda").bfloat16()
+    gate = torch.rand(rows, generator=gen, device="cuda")
+    wl, _ = B.make_workload(T, H, I, E, 4, 1, rows=rows)
     ws = B.Workspace(B.workspace_size(wl))
     out = torch.empty((T, H), device="cuda")
 
     def stage(C):
         out.fill_(float("nan"))
-        B.combine(x, w2, off, tid, gate, T=T, topk=k, num_consumers=C, out=out, workspace=ws)
+        B.combine(x, w2, off, tid, gate, T=T, topk=4, num_consumers=C, out=out, workspace=ws)
         return out.clone()
 
     ref = stage(3)
     for i in range(3):
         assert torch.equal(stage(0), ref), i
+    plan = _left_plan(ws)
+    print(f"plan: pad {plan[0]}, edge {plan[1]}, {plan[2]} edges, {plan[3]} bottoms", flush=True)
+    assert plan[1] == edge and pad in (None, plan[0])
     assert torch.equal(stage(3), ref) and ws.status() == 0
-    del x, w2
-    hidden, w1 = normal(T, H), normal(E, H, 2 * I) * H ** -0.5
+
+
+@pytest.mark.parametrize("name", list(UP_LARGE))
+def test_up_projection_full_tiles_with_smaller_ones(gpu_lib, name):
+    """Against fp32 torch (the bound of test_up_projection_tiles), three calls."""
+    import torch
+
+    from paper_2609_07536_amd import binding as B
+    E, N, H, rows_of = UP_LARGE[name]
+    I = N // 2
+    rows, T, off, tid = _routing(E, rows_of)
+    print(f"{name}: E={E} H={H} I={I} T={T} rows={rows}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    hidden = torch.randn((T, H), generator=gen, device="cuda").bfloat16()
+    w1 = (torch.randn((E, H, N), generator=gen, device="cuda") * H ** -0.5).bfloat16()
     packed, ref = B.pack_w1(w1), torch.empty((rows, I), device="cuda")
     bounds = off.tolist()
     for e in range(E):
@@ -219,8 +282,7 @@ def test_several_smaller_tiles_per_workgroup(gpu_lib, name):
         h = hidden[tid[a:b].long()].float() @ w1[e].float()
         ref[a:b] = torch.nn.functional.silu(h[:, :I]) * h[:, I:]
     for i in range(3):
-        got = B.gemm1_swiglu(hidden, packed, off, tid, k, rows)
-        # (the bound of test_up_projection_tiles)
+        got = B.gemm1_swiglu(hidden, packed, off, tid, 4, rows)
         assert (got.float() - ref).abs().le(2 ** -8 * ref.abs() + 2e-4).all(), i
 
 

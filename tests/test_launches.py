@@ -126,3 +126,40 @@ assert call("combine", T=300, H=512, I=64, E=8, topk=2, C=0) == 0
 result = launches()[-1][0]
 ''', MOE_GEMM2_SPIN_LIMIT=limit)
     assert ("moe_gemm2_fused" in got) == persistent, got
+
+
+TILE_NAMES = {"SmallTile<64, 64, 4, 2, 4, 64>": "64x64", "SmallTile<64, 128, 8, 4, 3, 64>": "64x128 deep",
+              "SmallTile<64, 128, 8, 4, 2, 64>": "64x128", "SmallTile<128, 128, 8, 4, 2, 64>": "128x128",
+              "SmallTile<128, 256, 8, 4, 3, 32>": "128x256"}
+
+
+def test_gpu_cases_run_as_the_tiles_they_name(recorder):
+    """The GPU tests of the launches without dedicated consumers reach every kind
+    of tile, each case the one it is for."""
+    import test_gpu_small_batch as cases
+    want, calls = [], []
+    for name, make in cases.CASES.items():
+        w = make()
+        calls.append(["combine", w.T, w.H, w.I, w.E, w.topk, w.L, w.Mtot])
+        want.append(cases.TILES[name])
+    for name, (E, H, I, T, k) in cases.UP.items():
+        calls.append(["gemm1", T, H, I, E, k, 1, T * k])
+        want.append(cases.UP_TILES[name])
+    for E, H, I, rows_of, _, _ in cases.LARGE.values():
+        rows = sum(rows_of(e) for e in range(E))
+        calls.append(["combine", -(-rows // 4), H, I, E, 4, 1, rows])
+        want.append("full")
+    for E, N, H, rows_of in cases.UP_LARGE.values():
+        rows = sum(rows_of(e) for e in range(E))
+        calls.append(["gemm1", -(-rows // 4), H, N // 2, E, 4, 1, rows])
+        want.append("full")
+    got = launch_recorder.run(recorder, f'''
+result = []
+for op, T, H, I, E, k, L_, rows in {calls}:
+    assert call(op, T, H, I, E, k, splits=L_, rows=rows) >= 0
+    result.append([c[0] for c in launches() if "fill_zero" not in c[0]][0])
+''')
+    kinds = ["full" if "mixed" in g else TILE_NAMES[g[g.index("<") + 1:g.index(">") + 1]] for g in got]
+    assert kinds == want, [x for x in zip(calls, kinds, want) if x[1] != x[2]]
+    for up in (False, True):
+        assert {k for k, c in zip(kinds, calls) if (c[0] == "gemm1") == up} == {*TILE_NAMES.values(), "full"}
