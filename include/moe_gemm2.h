@@ -20,10 +20,13 @@
  * "Wave-Quantized Pipeline Model" and Algorithm 1) to choose it.
  *
  * Calls that ask for no dedicated consumers (num_consumers 0 or -1, no
- * trace; the atomic scatter while rows <= T topk) run instead as two launches without flags or waits: a
- * grouped GEMM whose tile sizes follow the batch, then the combine.  Both
- * ways compute every output element by the same operations in the same
- * order, so their results are bitwise equal.
+ * trace; the atomic scatter while rows <= T topk) run instead as two launches
+ * without flags or waits: a grouped GEMM whose tile sizes follow the batch,
+ * then the combine.  The owner-write results of both ways are bitwise equal:
+ * every output element is the same operations in the same order.  The
+ * selector models the one launch: what it picks is the best C for callers who
+ * want dedicated consumers, and the two launches are as fast or faster than
+ * every C of it on the measured workloads.
  *
  * Conventions for every function:
  *   - all functions are extern "C"; none throws, aborts or prints;
@@ -345,8 +348,8 @@ int moe_gemm2_workspace_init(void* workspace, size_t workspace_bytes, void* stre
  * Values inside device arrays are checked by the kernel, which skips bad
  * entries and records MOE_ERR_BAD_ROUTING for moe_gemm2_status.
  * Launches on other streams may share the GPU: the two launches of a call
- * without dedicated consumers never wait; in the persistent kernel compute workgroups never
- * wait while they hold tiles, with C = 0 a workgroup waits on other
+ * without dedicated consumers never wait; in the persistent kernel compute
+ * workgroups never wait while they hold tiles, with C = 0 a workgroup waits on other
  * workgroups' tiles only once its whole grid has started, and dedicated
  * consumers (C >= 1) wait only on compute workgroups, which never wait; so
  * concurrent launches drain as long as their dedicated consumers together
@@ -401,7 +404,9 @@ int moe_gemm2_combine_traced(const void* x_perm, const void* w2, const int32_t* 
  *           and flagged; the topk bound per token is not checked (every
  *           in-range row is added).  With num_consumers 0 or -1, no trace and
  *           rows <= T topk the same additions run as the second of the two
- *           launches, one wave per token, without atomics;
+ *           launches: one wave per token sums its first topk rows, without
+ *           atomics, and rows past them are added by atomics, spread over
+ *           the launch;
  *   mode 2  owner-write over token bands: the wl->splits = L pipeline
  *           splits cut the routed rows instead of the columns.  Expert
  *           e's n_e = ceil(M_e/256) m-tiles are cut into L runs, band b
@@ -451,8 +456,8 @@ int moe_gemm2_combine_ex(const void* x_perm, const void* w2, const int32_t* expe
  *   - The device status word (MOE_ERR_TIMEOUT, MOE_ERR_BAD_ROUTING) lives
  *     in the scratch and is not reported; bad routing entries are skipped
  *     and waits are bounded as for moe_gemm2_combine.
- * Returns the number of consumer workgroups launched (>= 0) or a negative
- * status as moe_gemm2_combine_ex does. */
+ * Returns the number of consumer workgroups asked for or chosen (>= 0) or a
+ * negative status as moe_gemm2_combine_ex does. */
 #define MOE_GEMM2_NOALLOC_SCRATCH_BYTES (96u << 20)
 int moe_gemm2_combine_noalloc(const void* x_perm, const void* w2, const int32_t* expert_offsets,
                               const int32_t* token_ids, const float* gate_w, float* out,
@@ -527,11 +532,11 @@ int moe_gemm1_swiglu(const void* hidden, const void* w1, const int32_t* expert_o
 size_t moe_layer_workspace_size(const moe_workload_t* wl);
 
 /* The post-router layer: moe_gemm1_swiglu into the workspace's x_perm, then
- * moe_gemm2_combine on it (same stream, two launches).  Arguments as for
+ * moe_gemm2_combine on it (same stream; the up-projection's launch, then the
+ * stage's).  Arguments as for
  * those two functions; workspace of at least moe_layer_workspace_size(wl)
  * bytes, 256-byte aligned, zeroed once by moe_gemm2_workspace_init.  Shapes
- * must satisfy both functions' limits.  Returns the number of consumer
- * workgroups of the second launch (>= 0) or a negative status. */
+ * must satisfy both functions' limits.  Returns what moe_gemm2_combine does. */
 int moe_layer_forward(const void* hidden, const void* w1, const void* w2,
                       const int32_t* expert_offsets, const int32_t* token_ids,
                       const float* gate_w, float* out, const moe_workload_t* wl,

@@ -19,15 +19,15 @@
 // once to bf16, the rows of a token summed in ascending order.  So a
 // reduction is never split over waves, and the results are bitwise equal.
 //
-// Measured (us, GPU time, persistent kernel -> this path), H = 2048, I = 704,
-// E = 32, top-6, uniform routing: T = 1 36.7 -> 9.8, 8 40.7 -> 17.9,
-// 64 44.0 -> 21.3, 256 46.4 -> 22.3, 512 49.6 -> 26.5, 1024 55.9 -> 40,
-// 2048 80 -> 61, 4096 124.9 -> 104, 8192 200 -> 187, 16384 359 -> 347,
-// 32768 777 -> 751; its up-projection T = 1 44.3 -> 12.3, 64 46.6 -> 28.4,
-// 256 47.3 -> 29.7, 512 48.2 -> 33.5, 2048 104 -> 90, 4096 160 -> 148,
-// 16384 526 -> 504.  The largest GEMMs are bound by the power the chip may
-// draw: the up-projection of T = 16384 takes 553 us with random operands and
-// 405 us with zeros, and 526 us whether or not its loads hit the L2.
+// Measured (us a call, two sets of inputs in turn, persistent kernel -> this
+// path), H = 2048, I = 704, E = 32, top-6, uniform routing: T = 64 42.3 -> 20.6,
+// 256 45.6 -> 21.9, 512 49.4 -> 27.5, 1024 56.5 -> 38.8, 2048 81.6 -> 70.2, 4096
+// 128 -> 118, 8192 237 -> 202, 16384 426 -> 389, 32768 789 -> 763 (T = 1, GPU time
+// alone, 36.7 -> 9.8); its up-projection T = 64 59.7 -> 39.0, 256 60.5 -> 41.6, 512
+// 62.6 -> 49.4, 1024 67.1 / 68.9, 2048 117 -> 105, 4096 174 -> 161, 8192 293 ->
+// 284, 16384 567 -> 535.  The largest GEMMs are bound by the power the chip may
+// draw: the up-projection of T = 16384 takes 515 us on one set of random operands
+// and 396 us on zeros.
 #pragma once
 
 // A tile of BM rows x BN columns, its NW waves WNW along the columns, a ring
@@ -610,7 +610,7 @@ __device__ __forceinline__ MixedPlan mixed_plan(const Args& a, int P) {
   // before, computes them, E times the rows at most).
   if (!RowGather<Args>::on && all > (int)((a.rows + kBM - 1) / kBM) + a.E)
     return {kBM - 1, false, 0, 0, 0, 0, 0, 0};
-  // one round of full tiles holds everything (nothing to weigh: 3 us less)
+  // one round of full tiles holds everything: nothing to weigh
   const int whole = (N + kBN - 1) / kBN;
   if (all <= small_div(P, whole)) return {kBM - 1, false, whole, all * whole, 0, 0, 0, 0};
   const int fc_far = RowGather<Args>::on ? 166 * nk + 550 : 166 * nk + 150;
