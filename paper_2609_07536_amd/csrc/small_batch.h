@@ -106,9 +106,9 @@ __device__ __forceinline__ int small_n(const KArgs& a) { return a.H; }
 __device__ __forceinline__ int small_n(const G1Args& a) { return 2 * a.I; }
 
 // The rows of 64 K experts from e0 on, K neighbouring ones in each lane, by one
-// round trip (with K = 1 alone, E = 1024 experts took a wave 16 of them: the
-// stage of H = 2048, I = 256, 16 rows each 574 us). Clamped as in load_experts;
-// experts past E are empty.
+// round trip (with K = 1 alone, E = 1024 experts took a wave 16 of them for each
+// tile: the stage of H = 1024, I = 256, 16 rows each 316 us, now 151).  Clamped as
+// in load_experts; experts past E are empty.
 template <int K>
 struct ExpertRows {
   int start[K], count[K];
@@ -502,8 +502,8 @@ __global__ void __launch_bounds__(C::kThr) small_gemm_kernel(Args a) {
 // tiles, as the plan says for one with and one without a tile of the last round.
 // (With a workgroup for every smaller tile that the host's bound allows, most
 // found out for themselves, on a CU of their own, that there was nothing for
-// them: T = 16384, H = 2048, I = 704, E = 32, up-projection 531.8 us, now 520.7,
-// and E = 1024, H = 512, I = 128, T = 16384 146 / 108.  The stage's P workgroups
+// them: up-projection, H = 2048, I = 704, E = 32, T = 16384 531.8 us, now 520.7;
+// H = 512, I = 128, E = 1024, 100 rows each 135, now 86.  The stage's P workgroups
 // wait for a full tile's stores before the first smaller one: 388.4 us against
 // 383.3 with further ones, which start meanwhile.  Handed out by counters in the
 // workspace, the smaller tiles waited for the counters: H = 2048, I = 512, E =
